@@ -67,63 +67,80 @@ __device__ __forceinline__ int wave_minmax(int v) {
 }
 
 
-// One MLS point, per lane of its G-lane group: lane k owns nodes k + G s (when < 27) of the
-// 3x3x3 block around the nearest node.  mls_setup finds each node, its offset d = x_k - x,
-// |d|^2 and whether it supports the point (|d| <= r_w); the caller then issues its field loads,
-// and mls_solve builds and solves the moment system while those loads are in flight.
-template <int G>
+// Candidate nodes of an MLS point.  With c the node nearest to the point x on each axis, every node
+// within r_w < 1.5 of x lies in the 3x3x3 block around c, but never more than 15 of the 27 can.  Per
+// axis, call c near, the neighbour on x's side second and the other one far, at distances f, 1 - f
+// and 1 + f (f <= 1/2).  For r_w^2 < 2:
+//   - two far axes never: (1 + f)^2 + (1 + f')^2 >= 2;
+//   - far on a and second on b excludes far on b and second on a (the third axis alike), since
+//     (1 + f)^2 + (1 - f')^2 + (1 + f')^2 + (1 - f)^2 >= 4 > 2 r_w^2: only the one whose far axis
+//     has the smaller f can be a support node, and the two f then differ by (2 - r_w^2) / 2 at least.
+// That leaves the 8 corners of the cell around x (near or second on each axis) and, per non-empty
+// set of axes, the node that is far on the axis of the set with the smallest f, second on its other
+// axes and near off it: 8 + 7.  Corner i has second on the axes of the bits of i, far node i
+// belongs to the set FAR_SETS[i]; a point has 16 slots, and pair i holds corner i and far node i.
+// r_w^2 >= MLS_COMPACT_RW2 (the selection runs in FP32, so the bound leaves a margin) takes WIDE:
+// all 27 nodes.
+constexpr unsigned FAR_SETS = 0x07563421u;   // nibble i: axes x, y, z, xy, yz, xz, xyz, none
+
+// One MLS point, per lane of its G-lane group.  Compact: 8 pairs of slots (corner, far node), lane
+// l of 8 holds pair l (lanes 4..7 in reverse order, see gsum), lane l of 4 the pairs l and l + 4.
+// WIDE: lane l holds nodes l + G s of the block.
+template <int G, bool WIDE>
 struct MlsLane {
-    static constexpr int N = (27 + G - 1) / G;   // stencil nodes per lane
-    bool active[N];
-    int gx[N], gy[N], gz[N];
-    double d0[N], d1[N], d2[N], r2[N];
-    double phi[N];
-    double gr[N][3];
+    static constexpr int N = WIDE ? (27 + G - 1) / G : 16 / G;   // slots per lane
+    int c[3];                    // node nearest to the point (unwrapped)
+    int o[N][3];                 // slot's node relative to c
+    bool active[N];              // within r_w of the point
+    double d[N][3];              // x_k - x
+    double W[N], phi[N];
 };
 
-template <int G>
-__device__ __forceinline__ void mls_setup(const JobDev& J, const double xp[3], double rw2, int lane,
-                                          MlsLane<G>& m, int& err) {
-    constexpr int MLS_NODES = MlsLane<G>::N;
-    const int c0 = (int)floor(xp[0] + 0.5), c1 = (int)floor(xp[1] + 0.5), c2 = (int)floor(xp[2] + 0.5);
-    const int dims[3] = {J.nx, J.ny, J.nz};
-    // the nearest node wrapped once per periodic axis; its neighbours then wrap by +-n
-    int cw[3] = {c0, c1, c2};
-    for (int a = 0; a < 3; ++a)
-        if (J.bc[2 * a] == 0) {
-            cw[a] %= dims[a];
-            if (cw[a] < 0) cw[a] += dims[a];
-        }
+template <int G, bool WIDE>
+__device__ __forceinline__ void mls_locate(const double xp[3], double rw2, int lane, MlsLane<G, WIDE>& m) {
+    double dn[3];
+    int sg[3];       // direction of the second node
+    float f[3];
 #pragma unroll
-    for (int s = 0; s < MLS_NODES; ++s) {
-        const int k = lane + G * s;
-        m.active[s] = false;
-        m.d0[s] = m.d1[s] = m.d2[s] = 0.0;
-        m.r2[s] = 4.0 * rw2;
-        m.gr[s][0] = m.gr[s][1] = m.gr[s][2] = 0.0;
-        m.gx[s] = m.gy[s] = m.gz[s] = 0;
-        if (k >= 27) continue;
-        int nn[3] = {c0 + k % 3 - 1, c1 + (k / 3) % 3 - 1, c2 + k / 9 - 1};
-        m.d0[s] = nn[0] - xp[0];
-        m.d1[s] = nn[1] - xp[1];
-        m.d2[s] = nn[2] - xp[2];
-        m.r2[s] = m.d0[s] * m.d0[s] + m.d1[s] * m.d1[s] + m.d2[s] * m.d2[s];
-        m.active[s] = m.r2[s] <= rw2;
-        for (int a = 0; a < 3; ++a) {
-            const int bc = J.bc[2 * a];
-            if (bc == 0) {
-                nn[a] = cw[a] + (a == 0 ? k % 3 - 1 : (a == 1 ? (k / 3) % 3 - 1 : k / 9 - 1));
-                if (nn[a] < 0) nn[a] += dims[a];
-                else if (nn[a] >= dims[a]) nn[a] -= dims[a];
+    for (int a = 0; a < 3; ++a) {
+        const double n = floor(xp[a] + 0.5);
+        m.c[a] = (int)n;
+        dn[a] = n - xp[a];   // exact, and so is the offset added below
+        sg[a] = dn[a] > 0.0 ? -1 : 1;
+        f[a] = fabsf((float)dn[a]);
+    }
+#pragma unroll
+    for (int s = 0; s < MlsLane<G, WIDE>::N; ++s) {
+        bool some = true;
+        if (WIDE) {
+            const int k = lane + G * s;
+            some = k < 27;
+            m.o[s][0] = k % 3 - 1;
+            m.o[s][1] = (k / 3) % 3 - 1;
+            m.o[s][2] = some ? k / 9 - 1 : 0;
+        } else {
+            const int i = G == 8 ? (lane < 4 ? lane : 11 - lane) : lane + 4 * (s / 2);
+            if (s % 2 == 0) {
+#pragma unroll
+                for (int a = 0; a < 3; ++a) m.o[s][a] = (i >> a) & 1 ? sg[a] : 0;
             } else {
-                const int lo = bc == 1 ? 1 : 0, hi = bc == 1 ? dims[a] - 2 : dims[a] - 1;
-                if (nn[a] < lo || nn[a] > hi) {
-                    if (m.active[s]) err |= FLAG_DOMAIN;
-                    nn[a] = nn[a] < lo ? lo : hi;
-                }
+                const unsigned set = (FAR_SETS >> (4 * i)) & 7u;
+                const float f0 = set & 1u ? f[0] : 4.f, f1 = set & 2u ? f[1] : 4.f, f2 = set & 4u ? f[2] : 4.f;
+                const bool far0 = f0 <= f1 && f0 <= f2, far1 = !far0 && f1 <= f2;
+                some = set != 0u;
+                m.o[s][0] = set & 1u ? (far0 ? -sg[0] : sg[0]) : 0;
+                m.o[s][1] = set & 2u ? (far1 ? -sg[1] : sg[1]) : 0;
+                m.o[s][2] = set & 4u ? (far0 || far1 ? sg[2] : -sg[2]) : 0;
             }
         }
-        m.gx[s] = nn[0]; m.gy[s] = nn[1]; m.gz[s] = nn[2];
+        double r2 = 0.0;
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+            m.d[s][a] = dn[a] + (double)m.o[s][a];
+            r2 = a == 0 ? m.d[s][a] * m.d[s][a] : fma(m.d[s][a], m.d[s][a], r2);
+        }
+        m.active[s] = some && r2 <= rw2;
+        m.W[s] = r2;
     }
 }
 
@@ -135,102 +152,154 @@ __device__ __forceinline__ double rcp64(double x) {
     return r;
 }
 
-// Shape functions phi_k = [A^{-1} W_k p_k]_0 and (optionally) their gradients, A = sum W p p^T,
-// p = (1, d), W = exp(-(|d| / (r_w alpha))^2) (Eqs. l2norm, intKernel).  The weights are
-// evaluated in FP32; the moment matrix is accumulated and factorised (A = L D L^T, unit L) in
-// FP64 on every lane.
-template <int G>
-__device__ __forceinline__ void mls_solve(MlsLane<G>& m, float wq, bool want_grad, int& err) {
-    constexpr int MLS_NODES = MlsLane<G>::N;
-    double W[MLS_NODES];
-    double s00 = 0, s01 = 0, s02 = 0, s03 = 0, s11 = 0, s12 = 0, s13 = 0, s22 = 0, s23 = 0, s33 = 0;
-#pragma unroll
-    for (int s = 0; s < MLS_NODES; ++s) {
-        W[s] = m.active[s] ? (double)expf(-wq * (float)m.r2[s]) : 0.0;
-        const double w = W[s], d0 = m.d0[s], d1 = m.d1[s], d2 = m.d2[s];
-        s00 += w; s01 += w * d0; s02 += w * d1; s03 += w * d2;
-        s11 += w * d0 * d0; s12 += w * d0 * d1; s13 += w * d0 * d2;
-        s22 += w * d1 * d1; s23 += w * d1 * d2; s33 += w * d2 * d2;
+// Sum over the point's lanes of a per-lane value given as the lane's sums over its pairs of slots.
+// Four lanes hold two pairs each (p0, p1), eight lanes one: the tree adds pair i and pair i + 4
+// first in both, so the two forms give the same bits (and a job the same results in both).
+template <int G, bool WIDE>
+__device__ __forceinline__ double psum(double p0, double p1) {
+    if (G == 4) {
+        double v = p0 + p1;
+        v += dpp_f64<0xB1>(v);
+        v += dpp_f64<0x4E>(v);
+        return v;
     }
-    const double a00 = gsum<G>(s00), a01 = gsum<G>(s01), a02 = gsum<G>(s02), a03 = gsum<G>(s03);
-    const double a11 = gsum<G>(s11), a12 = gsum<G>(s12), a13 = gsum<G>(s13);
-    const double a22 = gsum<G>(s22), a23 = gsum<G>(s23), a33 = gsum<G>(s33);
+    p0 += dpp_f64<0x141>(p0);   // row_half_mirror: lane 7 - l holds pair l + 4
+    p0 += dpp_f64<0xB1>(p0);
+    p0 += dpp_f64<0x4E>(p0);
+    return p0;
+}
+
+// sum_k c_k q_k over the point for per-slot coefficients and values
+template <int G, bool WIDE>
+__device__ __forceinline__ double pdot(const double* c, const double* q) {
+#pragma clang fp contract(off)
+    constexpr int N = MlsLane<G, WIDE>::N, PAIRS = !WIDE && G == 4 ? 2 : 1;
+    double t[PAIRS];
+#pragma unroll
+    for (int s = 0; s < N; ++s) {
+        double& a = t[PAIRS == 2 ? s / 2 : 0];
+        a = s == 0 || (PAIRS == 2 && s == 2) ? c[s] * q[s] : fma(c[s], q[s], a);
+    }
+    return psum<G, WIDE>(t[0], t[PAIRS - 1]);
+}
+
+// Moment matrix A = sum W p p^T, p = (1, d), W = exp(-(|d| / (r_w alpha))^2) (Eqs. l2norm,
+// intKernel), factorised as L D L^T (unit L) in FP64 on every lane; the weights are evaluated in
+// FP32.  phi_k = [A^{-1} W_k p_k]_0; with GRAD, gn_k = n . [A^{-1} W_k p_k]_{1..3} and the rows
+// themselves in gr (the diffuse derivatives along n and along the axes).
+// Products and sums are written as explicit multiplications and fused multiply-adds with
+// contraction off, so that the four- and eight-lane forms round alike.
+template <int G, bool WIDE, bool GRAD>
+__device__ __forceinline__ void mls_solve(MlsLane<G, WIDE>& m, float wq, int& err, const double* nrm = nullptr,
+                                          double (*gr)[3] = nullptr, double* gn = nullptr) {
+#pragma clang fp contract(off)
+    constexpr int N = MlsLane<G, WIDE>::N;
+    constexpr int PAIRS = !WIDE && G == 4 ? 2 : 1;   // sums kept apart per pair (see psum)
+    double t[PAIRS][10];
+#pragma unroll
+    for (int s = 0; s < N; ++s) {
+        const double w = m.active[s] ? (double)expf(-wq * (float)m.W[s]) : 0.0;
+        m.W[s] = w;
+        const double d0 = m.d[s][0], d1 = m.d[s][1], d2 = m.d[s][2];
+        const double w0 = w * d0, w1 = w * d1, w2 = w * d2;
+        double* q = t[PAIRS == 2 ? s / 2 : 0];
+        if (s == 0 || (PAIRS == 2 && s == 2)) {
+            q[0] = w; q[1] = w0; q[2] = w1; q[3] = w2;
+            q[4] = w0 * d0; q[5] = w0 * d1; q[6] = w0 * d2;
+            q[7] = w1 * d1; q[8] = w1 * d2; q[9] = w2 * d2;
+        } else {
+            q[0] += w; q[1] += w0; q[2] += w1; q[3] += w2;
+            q[4] = fma(w0, d0, q[4]); q[5] = fma(w0, d1, q[5]); q[6] = fma(w0, d2, q[6]);
+            q[7] = fma(w1, d1, q[7]); q[8] = fma(w1, d2, q[8]); q[9] = fma(w2, d2, q[9]);
+        }
+    }
+    double A[10];
+#pragma unroll
+    for (int k = 0; k < 10; ++k) A[k] = psum<G, WIDE>(t[0][k], t[PAIRS - 1][k]);
+    const double a01 = A[1], a02 = A[2], a03 = A[3];
     // A = L D L^T
-    const double e0 = a00;
-    if (!(e0 > 0.0)) err |= FLAG_NONFINITE;
-    const double i0 = rcp64(e0);
+    const double e0 = A[0], i0 = rcp64(e0);
     const double l10 = a01 * i0, l20 = a02 * i0, l30 = a03 * i0;
-    const double e1 = a11 - l10 * a01;
-    if (!(e1 > 0.0)) err |= FLAG_NONFINITE;
-    const double i1 = rcp64(e1);
-    const double b21 = a12 - l20 * a01, b31 = a13 - l30 * a01;   // D-scaled column entries
+    const double e1 = fma(-l10, a01, A[4]), i1 = rcp64(e1);
+    const double b21 = fma(-l20, a01, A[5]), b31 = fma(-l30, a01, A[6]);   // D-scaled column entries
     const double l21 = b21 * i1, l31 = b31 * i1;
-    const double e2 = a22 - l20 * a02 - l21 * b21;
-    if (!(e2 > 0.0)) err |= FLAG_NONFINITE;
-    const double i2 = rcp64(e2);
-    const double b32 = a23 - l30 * a02 - l31 * b21;
+    const double e2 = fma(-l21, b21, fma(-l20, a02, A[7])), i2 = rcp64(e2);
+    const double b32 = fma(-l31, b21, fma(-l30, a02, A[8]));
     const double l32 = b32 * i2;
-    const double e3 = a33 - l30 * a03 - l31 * b31 - l32 * b32;
-    if (!(e3 > 0.0)) err |= FLAG_NONFINITE;
-    const double i3 = rcp64(e3);
+    const double e3 = fma(-l32, b32, fma(-l31, b31, fma(-l30, a03, A[9]))), i3 = rcp64(e3);
+    if (!(e0 > 0.0 && e1 > 0.0 && e2 > 0.0 && e3 > 0.0)) err |= FLAG_NONFINITE;
 #pragma unroll
-    for (int s = 0; s < MLS_NODES; ++s) {
+    for (int s = 0; s < N; ++s) {
         // v = A^{-1} p_k: L y = p, z = D^{-1} y, L^T v = z
-        const double y0 = 1.0;
-        const double y1 = m.d0[s] - l10 * y0;
-        const double y2 = m.d1[s] - l20 * y0 - l21 * y1;
-        const double y3 = m.d2[s] - l30 * y0 - l31 * y1 - l32 * y2;
+        const double y1 = m.d[s][0] - l10;
+        const double y2 = fma(-l21, y1, m.d[s][1] - l20);
+        const double y3 = fma(-l32, y2, fma(-l31, y1, m.d[s][2] - l30));
         const double v3 = y3 * i3;
-        const double v2 = y2 * i2 - l32 * v3;
-        const double v1 = y1 * i1 - l21 * v2 - l31 * v3;
-        const double v0 = y0 * i0 - l10 * v1 - l20 * v2 - l30 * v3;
-        m.phi[s] = W[s] * v0;
-        if (want_grad) { m.gr[s][0] = W[s] * v1; m.gr[s][1] = W[s] * v2; m.gr[s][2] = W[s] * v3; }
+        const double v2 = fma(-l32, v3, y2 * i2);
+        const double v1 = fma(-l31, v3, fma(-l21, v2, y1 * i1));
+        const double v0 = fma(-l30, v3, fma(-l20, v2, fma(-l10, v1, i0)));
+        const double w = m.W[s];
+        m.phi[s] = w * v0;
+        if (GRAD) {
+            gr[s][0] = w * v1; gr[s][1] = w * v2; gr[s][2] = w * v3;
+            gn[s] = fma(gr[s][2], nrm[2], fma(gr[s][1], nrm[1], gr[s][0] * nrm[0]));
+        }
     }
 }
 
-// Window-local index of a node, or -1 if outside.
-__device__ __forceinline__ long long win_index(const JobDev& J, const WinDesc& d, int gx, int gy,
-                                               int gz) {
-    if (d.w[0] < 1 || d.w[1] < 1 || d.w[2] < 1 || d.w[0] > J.nx || d.w[1] > J.ny || d.w[2] > J.nz)
-        return -1;
-    int lx = gx - d.o[0], ly = gy - d.o[1], lz = gz - d.o[2];
-    if (lx < 0) lx += J.nx;
-    if (ly < 0) ly += J.ny;
-    if (lz < 0) lz += J.nz;
-    if (lx >= d.w[0] || ly >= d.w[1] || lz >= d.w[2]) return -1;
-    return lx + (long long)d.w[0] * (ly + (long long)d.w[1] * lz);
-}
-
-// Moments (rho - 1, u*) of the lane's active stencil nodes from the body's moment window.
-// md: the layout of the moment window, which callers load with their other early reads
-template <int G>
-__device__ __forceinline__ void mls_moments(const Pools& P, const JobDev& J, const BodyDev& B, const WinDesc& md,
-                                            const MlsLane<G>& m, float4 mom[MlsLane<G>::N], int& err) {
-    constexpr int MLS_NODES = MlsLane<G>::N;
+// Index of every slot's node in a window of layout d (see WinDesc).  Points whose 3x3x3 block lies
+// inside the window and the fluid, every point of an ordinary step, take the first form (one vote
+// per wave): no wrap, no test per node, and the inactive slots hold valid indices too, so the
+// caller loads all of them without a branch.  The second form wraps periodic axes, reports support
+// nodes beyond a wall or the window, and gives their slots index 0.
+template <int G, bool WIDE>
+__device__ __forceinline__ void mls_index(const JobDev& J, const WinDesc& d, MlsLane<G, WIDE>& m,
+                                          unsigned idx[MlsLane<G, WIDE>::N], int& err) {
+    constexpr int N = MlsLane<G, WIDE>::N;
+    const int n[3] = {J.nx, J.ny, J.nz};
+    const int s1 = d.w[0], s2 = d.w[0] * d.w[1];
+    bool in = s2 < (1 << 23);   // 24-bit products below
+    int lo[3], hi[3];
 #pragma unroll
-    for (int s = 0; s < MLS_NODES; ++s) {
-        mom[s] = make_float4(0.f, 0.f, 0.f, 0.f);
-        if (!m.active[s]) continue;
-        const long long l = win_index(J, md, m.gx[s], m.gy[s], m.gz[s]);
-        if (l < 0) err |= FLAG_WINDOW;
-        else mom[s] = P.mwin[B.win_off + l];
+    for (int a = 0; a < 3; ++a) {
+        const int bc = J.bc[2 * a];
+        lo[a] = bc == 0 ? -0x40000000 : (bc == 1 ? 1 : 0);
+        hi[a] = bc == 0 ? 0x40000000 : (bc == 1 ? n[a] - 2 : n[a] - 1);
+        in = in && m.c[a] > max(lo[a], d.b[a]) && m.c[a] < min(hi[a], d.b[a] + d.w[a] - 1);
     }
-}
-
-// sum_k c_k q_k over the group for per-node coefficients c (phi or a gradient row) and field
-// values q (component `comp` of the moments: 0 rho - 1, 1..3 u*)
-template <int G>
-__device__ __forceinline__ double group_dot(const double* c, int cstride, const float4 mom[MlsLane<G>::N],
-                                            int comp) {
-    constexpr int MLS_NODES = MlsLane<G>::N;
-    double acc = 0.0;
+    if (__all(in)) {
+        const int base = (m.c[0] - d.b[0]) + s1 * (m.c[1] - d.b[1]) + s2 * (m.c[2] - d.b[2]);
 #pragma unroll
-    for (int s = 0; s < MLS_NODES; ++s) {
-        const float q = comp == 0 ? mom[s].x : (comp == 1 ? mom[s].y : (comp == 2 ? mom[s].z : mom[s].w));
-        acc += c[s * cstride] * (double)q;
+        for (int s = 0; s < N; ++s)
+            idx[s] = (unsigned)(base + m.o[s][0] + __mul24(m.o[s][1], s1) + __mul24(m.o[s][2], s2));
+        return;
     }
-    return gsum<G>(acc);
+#pragma unroll
+    for (int s = 0; s < N; ++s) {
+        unsigned i = 0, st = 1;
+        bool ok = true;
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+            int u = m.c[a] + m.o[s][a];
+            if (J.bc[2 * a] != 0 && (u < lo[a] || u > hi[a])) {
+                if (m.active[s]) err |= FLAG_DOMAIN;
+                u = u < lo[a] ? lo[a] : hi[a];
+            }
+            int t = u - d.b[a];
+            if (J.bc[2 * a] == 0 && (t < 0 || t >= d.w[a])) {
+                t %= n[a];
+                if (t < 0) t += n[a];
+            }
+            ok = ok && t >= 0 && t < d.w[a];
+            i += (unsigned)t * st;
+            st *= (unsigned)d.w[a];
+        }
+        if (!ok) {
+            if (m.active[s]) err |= FLAG_WINDOW;
+            m.active[s] = false;
+        }
+        idx[s] = ok ? i : 0u;
+    }
 }
 
 __device__ __forceinline__ void load3(const double* p, double v[3]) { v[0] = p[0]; v[1] = p[1]; v[2] = p[2]; }
@@ -318,13 +387,16 @@ __device__ __forceinline__ WinDesc window_from_box(const JobDev& J, const BodyDe
         if (h < l) { flag |= FLAG_NONFINITE; l = 0; h = 0; }
         if (J.bc[2 * a] == 0) {
             const int w = h - l + 1;
-            if (w >= dims[a]) { d.o[a] = 0; d.w[a] = dims[a]; }
-            else { int o = l % dims[a]; if (o < 0) o += dims[a]; d.o[a] = o; d.w[a] = w; }
+            int o = l % dims[a];
+            if (o < 0) o += dims[a];
+            if (w >= dims[a]) { d.o[a] = 0; d.w[a] = dims[a]; d.b[a] = l - o; }
+            else { d.o[a] = o; d.w[a] = w; d.b[a] = l; }
         } else {
             if (l < 0) l = 0;
             if (h > dims[a] - 1) h = dims[a] - 1;
             d.o[a] = l < dims[a] ? l : dims[a] - 1;
             d.w[a] = h >= l ? h - l + 1 : 1;
+            d.b[a] = d.o[a];
         }
         if (d.w[a] > B.win_cap[a]) { flag |= FLAG_WINDOW; d.w[a] = B.win_cap[a]; }
         if (d.w[a] < 1) d.w[a] = 1;
@@ -393,35 +465,34 @@ __device__ __forceinline__ long long fix_rn(double v) {
 // nodes per marker, but far fewer distinct nodes per marker over the block.  The
 // block therefore sums its contributions in LDS first (int64, so the order cannot change the
 // sum) and sends one global atomic per distinct node and component.  The LDS box is the
-// bounding box of the block's 3x3x3 stencils in unwrapped node coordinates; a block whose box
-// exceeds SPREAD_LDS_NODES (markers far apart on the lattice) adds straight to global memory.
+// bounding box of the block's 3x3x3 stencils in unwrapped node coordinates, laid out with fixed
+// strides of 8 and 64, so its cells are addressed by shifts and a lane keeps its x and y through the
+// planes; a block whose box exceeds 8 x 8 x SPREAD_LDS_Z (markers far apart on the lattice) adds
+// straight to global memory.
 //
 // With fold set, the same block-wide reduction also folds the integer boxes that the vertex
 // blocks wrote for x^n into this step's force window (min / max, order independent): every
 // block derives the same descriptor and block 0 publishes it for the sweep and the moments.
 // vb[6] is the box of the vertex-block boxes this thread loaded.
 // Without fold, fd_in is the window the window kernel of the previous step published.
-constexpr int SPREAD_LDS_NODES = 256;
+constexpr int SPREAD_LDS_Z = 6;
 
-template <int G>
+template <int G, bool WIDE>
 __device__ __forceinline__ void spread_block(const Pools& P, const JobDev& J, const BodyDev& B, int b,
                                              int blk, bool fold, const int vb[6], const WinDesc& fd_in,
-                                             bool live, const int cen_node[3], const MlsLane<G>& m,
-                                             int lane, const long long fx[MlsLane<G>::N][3], int& err) {
-    constexpr int MLS_NODES = MlsLane<G>::N;
+                                             bool live, MlsLane<G, WIDE>& m,
+                                             const long long fx[MlsLane<G, WIDE>::N][3], int& err) {
+    constexpr int N = MlsLane<G, WIDE>::N;
     static_assert(IB_BLOCK == 64, "the block is one wave: its boxes are wave reductions");
-    __shared__ long long s_acc[3][SPREAD_LDS_NODES];
+    __shared__ unsigned long long s_acc[3][64 * SPREAD_LDS_Z];
     const long long capn = (long long)B.win_cap[0] * B.win_cap[1] * B.win_cap[2];
     unsigned long long* fw0 = (unsigned long long*)(P.fwin + 3 * B.win_off);
-    // stencil box of the live markers; with fold, the box of the vertex-block boxes
+    // stencil box of the block's markers; with fold, the box of the vertex-block boxes
     int o[3], w[3], bmin[3], bmax[3];
-    bool small = true;   // every side within the LDS box (also keeps the volume from overflowing)
+#pragma unroll
     for (int a = 0; a < 3; ++a) {
-        const int l = wave_minmax<false>(live ? cen_node[a] - 1 : 0x3fffffff);
-        const int h = wave_minmax<true>(live ? cen_node[a] + 1 : -0x3fffffff);
-        o[a] = l;
-        w[a] = h >= l ? h - l + 1 : 1;
-        small = small && w[a] <= SPREAD_LDS_NODES;
+        o[a] = wave_minmax<false>(m.c[a]) - 1;
+        w[a] = wave_minmax<true>(m.c[a]) + 2 - o[a];
         if (fold) {
             bmin[a] = wave_minmax<false>(vb[a]);
             bmax[a] = wave_minmax<true>(vb[3 + a]);
@@ -432,60 +503,67 @@ __device__ __forceinline__ void spread_block(const Pools& P, const JobDev& J, co
         fd = window_from_box(J, B, bmin, bmax, err);
         if (blk == 0 && threadIdx.x == 0) P.fdesc[b] = fd;
     }
-    const int vol = small ? w[0] * w[1] * w[2] : SPREAD_LDS_NODES + 1;
-    const bool use_lds = vol <= SPREAD_LDS_NODES;   // uniform over the block
-    if (use_lds) {
-        for (int i = threadIdx.x; i < vol; i += blockDim.x) s_acc[0][i] = s_acc[1][i] = s_acc[2][i] = 0;
-        __syncthreads();
-    }
-    if (live) {
+    const bool use_lds = w[0] <= 8 && w[1] <= 8 && w[2] <= SPREAD_LDS_Z;   // uniform over the block
+    unsigned idx[N];
+    if (!use_lds) {
+        mls_index<G, WIDE>(J, fd, m, idx, err);
 #pragma unroll
-        for (int sn = 0; sn < MLS_NODES; ++sn) {
-            if (!m.active[sn]) continue;
-            const long long l = win_index(J, fd, m.gx[sn], m.gy[sn], m.gz[sn]);
-            if (l < 0) {
-                err |= FLAG_WINDOW;
-                continue;
-            }
-            if (use_lds) {
-                const int k = lane + G * sn;
-                const int li = (cen_node[0] + k % 3 - 1 - o[0]) +
-                               w[0] * ((cen_node[1] + (k / 3) % 3 - 1 - o[1]) + w[1] * (cen_node[2] + k / 9 - 1 - o[2]));
+        for (int s = 0; s < N; ++s)
+            if (live && m.active[s])
                 for (int c = 0; c < 3; ++c)
-                    if (fx[sn][c]) atomicAdd((unsigned long long*)&s_acc[c][li], (unsigned long long)fx[sn][c]);
-            } else {
-                for (int c = 0; c < 3; ++c)
-                    if (fx[sn][c]) atomicAdd(fw0 + c * capn + l, (unsigned long long)fx[sn][c]);
-            }
+                    if (fx[s][c]) atomicAdd(fw0 + c * capn + idx[s], (unsigned long long)fx[s][c]);
+        return;
+    }
+    const int t = threadIdx.x;
+    for (int z = 0; z < w[2]; ++z)
+        for (int c = 0; c < 3; ++c) s_acc[c][64 * z + t] = 0;
+    __syncthreads();
+    if (live) {
+        const int base = (m.c[0] - o[0]) + 8 * (m.c[1] - o[1]) + 64 * (m.c[2] - o[2]);
+#pragma unroll
+        for (int s = 0; s < N; ++s) {
+            const int li = base + m.o[s][0] + 8 * m.o[s][1] + 64 * m.o[s][2];
+            if (m.active[s])
+                for (int c = 0; c < 3; ++c) atomicAdd(&s_acc[c][li], (unsigned long long)fx[s][c]);
         }
     }
-    if (!use_lds) return;
     __syncthreads();
-    const int dims[3] = {J.nx, J.ny, J.nz};
-    for (int i = threadIdx.x; i < vol; i += blockDim.x) {
-        const long long v0 = s_acc[0][i], v1 = s_acc[1][i], v2 = s_acc[2][i];
-        if (!(v0 | v1 | v2)) continue;
-        // back to wrapped lattice coordinates; only nodes with a window index received sums
-        // (a support node beyond a wall has already raised the domain error; it is dropped)
-        int g[3] = {o[0] + i % w[0], o[1] + (i / w[0]) % w[1], o[2] + i / (w[0] * w[1])};
-        bool inside = true;
-        for (int a = 0; a < 3; ++a) {
-            if (J.bc[2 * a] == 0) { g[a] %= dims[a]; if (g[a] < 0) g[a] += dims[a]; }
-            else if (g[a] < 0 || g[a] >= dims[a]) inside = false;
+    // flush: the lane's column of the box.  Only nodes that hold a sum are mapped to the window
+    // and added; a support node beyond a wall has raised the domain error and is dropped.
+    const int n[3] = {J.nx, J.ny, J.nz};
+    const int ux = o[0] + (t & 7), uy = o[1] + (t >> 3);
+    bool in = true;
+    int l[3] = {ux, uy, 0};
+    for (int a = 0; a < 2; ++a) {
+        const int u = l[a];
+        l[a] = u - fd.b[a];
+        if (J.bc[2 * a] == 0) {
+            if (l[a] < 0 || l[a] >= fd.w[a]) { l[a] %= n[a]; if (l[a] < 0) l[a] += n[a]; }
         }
-        const long long l = inside ? win_index(J, fd, g[0], g[1], g[2]) : -1;
-        if (l < 0) continue;
-        if (v0) atomicAdd(fw0 + l, (unsigned long long)v0);
-        if (v1) atomicAdd(fw0 + capn + l, (unsigned long long)v1);
-        if (v2) atomicAdd(fw0 + 2 * capn + l, (unsigned long long)v2);
+        in = in && l[a] >= 0 && l[a] < fd.w[a];
+    }
+    const unsigned s2 = (unsigned)fd.w[0] * (unsigned)fd.w[1];
+    const unsigned col = (unsigned)l[0] + (unsigned)fd.w[0] * (unsigned)l[1];
+    for (int z = 0; z < w[2]; ++z) {
+        const unsigned long long v0 = s_acc[0][64 * z + t], v1 = s_acc[1][64 * z + t], v2 = s_acc[2][64 * z + t];
+        int lz = o[2] + z - fd.b[2];   // uniform
+        if (J.bc[4] == 0 && (lz < 0 || lz >= fd.w[2])) { lz %= n[2]; if (lz < 0) lz += n[2]; }
+        if (!(v0 | v1 | v2)) continue;
+        if (!in || lz < 0 || lz >= fd.w[2]) {
+            err |= FLAG_WINDOW;
+            continue;
+        }
+        unsigned long long* f = fw0 + col + (unsigned long long)s2 * (unsigned)lz;
+        if (v0) atomicAdd(f, v0);
+        if (v1) atomicAdd(f + capn, v1);
+        if (v2) atomicAdd(f + 2 * capn, v2);
     }
 }
 
 // ---------------------------------------------------------------- centroids (+ hinges)
-// Batched launches ask for four waves per SIMD, as the probe kernel does (128 VGPRs, a 52 B spill).
-template <bool SOLO, int G>
+template <bool SOLO, int G, bool WIDE>
 __global__ void __launch_bounds__(IB_BLOCK, SOLO ? 1 : 4) k_centroids(Pools P, int nblk_tri, int fold) {
-    constexpr int MLS_NODES = MlsLane<G>::N, MLS_PER_BLOCK = IB_BLOCK / G;
+    constexpr int N = MlsLane<G, WIDE>::N, PTS = IB_BLOCK / G;
     if ((int)blockIdx.x >= nblk_tri) {
         // edge blocks: one thread per hinge of a membrane
         const int eb = blockIdx.x - nblk_tri;
@@ -501,13 +579,13 @@ __global__ void __launch_bounds__(IB_BLOCK, SOLO ? 1 : 4) k_centroids(Pools P, i
     }
     const int b = block_body<SOLO>(P, P.blk_body_c, blockIdx.x);
     const BodyDev& B = body_of<SOLO>(P, b);
-    const JobDev& J = body_job<SOLO>(P, B);
+    if ((B.rw2 >= MLS_COMPACT_RW2) != WIDE) return;   // the other form's launch
+    const JobDev J = body_job<SOLO>(P, B);   // copied before the first store: one round of scalar loads
     BodyState& S = P.bstate[b];
     const int grp = threadIdx.x / G, lane = threadIdx.x % G;
     const int blk = blockIdx.x - B.blk_c0;
-    const int t = blk * MLS_PER_BLOCK + grp;
-    const bool live = t < B.nt;
-    __shared__ double vol[MLS_PER_BLOCK];
+    const bool live = blk * PTS + grp < B.nt;
+    const int t = live ? blk * PTS + grp : B.nt - 1;   // a spare group repeats the last triangle
     int err = 0;
     // everything this block reads before its MLS work is loaded first, so that the latencies
     // overlap: the vertex-block boxes of x^n (fold) or the published window, the triangle's
@@ -524,203 +602,210 @@ __global__ void __launch_bounds__(IB_BLOCK, SOLO ? 1 : 4) k_centroids(Pools P, i
     } else {
         fd_pub = P.fdesc[b];
     }
-    double xa[3] = {0, 0, 0}, xb_[3] = {0, 0, 0}, xc[3] = {0, 0, 0}, Ub[3] = {0, 0, 0};
-    if (live) {
-        const int* tv = P.tri + 3 * (B.t0 + t);
-        load3(P.x + 3 * (B.v0 + tv[0]), xa);
-        load3(P.x + 3 * (B.v0 + tv[1]), xb_);
-        load3(P.x + 3 * (B.v0 + tv[2]), xc);
-        if (!B.rigid)
-            for (int a = 0; a < 3; ++a)
-                Ub[a] = (P.uv[3 * (B.v0 + tv[0]) + a] + P.uv[3 * (B.v0 + tv[1]) + a] +
-                         P.uv[3 * (B.v0 + tv[2]) + a]) * (1.0 / 3.0);
+    double xa[3], xb_[3], xc[3], Ub[3] = {0, 0, 0};
+    const int* tv = P.tri + 3 * (B.t0 + t);
+    load3(P.x + 3 * (B.v0 + tv[0]), xa);
+    load3(P.x + 3 * (B.v0 + tv[1]), xb_);
+    load3(P.x + 3 * (B.v0 + tv[2]), xc);
+    if (!B.rigid)
+        for (int a = 0; a < 3; ++a)
+            Ub[a] = (P.uv[3 * (B.v0 + tv[0]) + a] + P.uv[3 * (B.v0 + tv[1]) + a] +
+                     P.uv[3 * (B.v0 + tv[2]) + a]) * (1.0 / 3.0);
+    double cen[3], ab[3], ac[3], nn[3];
+    for (int a = 0; a < 3; ++a) {
+        cen[a] = (xa[a] + xb_[a] + xc[a]) * (1.0 / 3.0);
+        ab[a] = xb_[a] - xa[a];
+        ac[a] = xc[a] - xa[a];
     }
-    double Vt = 0.0;
-    int cen_node[3] = {0, 0, 0};               // node nearest to the centroid (unwrapped)
-    long long fx[MLS_NODES][3] = {};           // fixed-point force of each stencil node
-    MlsLane<G> m;
-    if (live) {
-        double cen[3], ab[3], ac[3], N[3];
-        for (int a = 0; a < 3; ++a) {
-            cen[a] = (xa[a] + xb_[a] + xc[a]) * (1.0 / 3.0);
-            ab[a] = xb_[a] - xa[a];
-            ac[a] = xc[a] - xa[a];
-        }
-        cross3(ab, ac, N);
-        const double A = 0.5 * sqrt(dot3(N, N));
-        if (lane == 0) {
-            // geometry at x^n for the probes of this step
-            double* g = P.tgeo + 6 * (B.t0 + t);
-            for (int a = 0; a < 3; ++a) { g[a] = cen[a]; g[3 + a] = N[a]; }
-        }
-        if (!B.rigid && B.kv != 0.0) {
-            // signed volume of the tetrahedron (r, a, b, c), r = vertex 0 of the body
-            double r0[3], pa[3], pb[3], pc[3], bc[3];
-            load3(P.x + 3 * B.v0, r0);
-            for (int a = 0; a < 3; ++a) { pa[a] = xa[a] - r0[a]; pb[a] = xb_[a] - r0[a]; pc[a] = xc[a] - r0[a]; }
-            cross3(pb, pc, bc);
-            Vt = dot3(pa, bc) * (1.0 / 6.0);
-        }
-        mls_setup<G>(J, cen, B.rw2, lane, m, err);
-        for (int a = 0; a < 3; ++a) cen_node[a] = (int)floor(cen[a] + 0.5);
-        float4 mom[MLS_NODES];
-        // a lone body's launch is a latency chain: its moment loads go out before the solve; a
-        // batched launch is throughput-bound and loads them after it, to hold fewer registers
-        if (SOLO) mls_moments<G>(P, J, B, md, m, mom, err);
-        mls_solve<G>(m, B.wq, false, err);
-        if (!SOLO) mls_moments<G>(P, J, B, md, m, mom, err);
-        const double U0 = group_dot<G>(m.phi, 1, mom, 1);
-        const double U1 = group_dot<G>(m.phi, 1, mom, 2);
-        const double U2 = group_dot<G>(m.phi, 1, mom, 3);
-        // desired boundary velocity U_b (Sec. 1.2): membranes average their vertex velocities,
-        // rigid bodies move the marker with the body
-        if (B.rigid) {
-            double rr[3] = {cen[0] - S.X[0], cen[1] - S.X[1], cen[2] - S.X[2]}, w[3];
-            cross3(S.om, rr, w);
-            for (int a = 0; a < 3; ++a) Ub[a] = S.u[a] + w[a];
-        }
-        // F_l = (U_b - U*) / dt, spread with c_l = A_l h (Eq. bodyforce), as int64 fixed point
+    MlsLane<G, WIDE> m;
+    mls_locate<G, WIDE>(cen, B.rw2, lane, m);
+    unsigned idx[N];
+    float4 mom[N];
+    mls_index<G, WIDE>(J, md, m, idx, err);
 #pragma unroll
-        for (int sn = 0; sn < MLS_NODES; ++sn) {
-            if (!m.active[sn]) continue;
-            const double sc = A * B.shell_h * m.phi[sn];
-            fx[sn][0] = fix_rn(sc * (Ub[0] - U0) * FIX_SCALE);
-            fx[sn][1] = fix_rn(sc * (Ub[1] - U1) * FIX_SCALE);
-            fx[sn][2] = fix_rn(sc * (Ub[2] - U2) * FIX_SCALE);
-        }
+    for (int s = 0; s < N; ++s) mom[s] = P.mwin[B.win_off + idx[s]];
+    cross3(ab, ac, nn);
+    const double A = 0.5 * sqrt(dot3(nn, nn));
+    if (live && lane == 0) {
+        // geometry at x^n for the probes of this step
+        double* g = P.tgeo + 6 * (B.t0 + t);
+        for (int a = 0; a < 3; ++a) { g[a] = cen[a]; g[3 + a] = nn[a]; }
     }
-    spread_block<G>(P, J, B, b, blk, fold != 0, vb, fd_pub, live, cen_node, m, lane, fx, err);
-    if (err) atomicOr(P.flags + B.job, err);
+    mls_solve<G, WIDE, false>(m, B.wq, err);
+    double U[3];
+    for (int a = 0; a < 3; ++a) {
+        double q[N];
+#pragma unroll
+        for (int s = 0; s < N; ++s) q[s] = a == 0 ? mom[s].y : (a == 1 ? mom[s].z : mom[s].w);
+        U[a] = pdot<G, WIDE>(m.phi, q);
+    }
+    // desired boundary velocity U_b (Sec. 1.2): membranes average their vertex velocities,
+    // rigid bodies move the marker with the body
+    if (B.rigid) {
+        double rr[3] = {cen[0] - S.X[0], cen[1] - S.X[1], cen[2] - S.X[2]}, w[3];
+        cross3(S.om, rr, w);
+        for (int a = 0; a < 3; ++a) Ub[a] = S.u[a] + w[a];
+    }
+    // F_l = (U_b - U*) / dt, spread with c_l = A_l h (Eq. bodyforce), as int64 fixed point
+    const double fs = A * B.shell_h * FIX_SCALE;
+    long long fx[N][3];   // fixed-point force of each slot's node
+    for (int a = 0; a < 3; ++a) U[a] = Ub[a] - U[a];
+#pragma unroll
+    for (int s = 0; s < N; ++s)
+        for (int a = 0; a < 3; ++a) fx[s][a] = fix_rn(fs * m.phi[s] * U[a]);
+    spread_block<G, WIDE>(P, J, B, b, blk, fold != 0, vb, fd_pub, live, m, fx, err);
+    if (err && live) atomicOr(P.flags + B.job, err);
     if (B.rigid || B.kv == 0.0) return;
-    if (lane == 0) vol[grp] = Vt;
+    // signed volume of the tetrahedron (r, a, b, c), r = vertex 0 of the body; one partial per
+    // VOL_GROUP triangles, folded into V by k_fold_bodies
+    __shared__ double vol[PTS];
+    if (lane == 0) {
+        double r0[3], pa[3], pb[3], pc[3], bc[3];
+        load3(P.x + 3 * B.v0, r0);
+        for (int a = 0; a < 3; ++a) { pa[a] = xa[a] - r0[a]; pb[a] = xb_[a] - r0[a]; pc[a] = xc[a] - r0[a]; }
+        cross3(pb, pc, bc);
+        vol[grp] = live ? dot3(pa, bc) * (1.0 / 6.0) : 0.0;
+    }
     __syncthreads();
-    double sv = 0.0;
-    for (int g = 0; g < MLS_PER_BLOCK; ++g) sv += vol[g];
-    if (threadIdx.x == 0) store_partials(P, B, blk, &sv, 1);   // folded into V by k_fold_bodies
+    constexpr int PARTS = PTS / VOL_GROUP;
+    const int part = blk * PARTS + (int)threadIdx.x;
+    if ((int)threadIdx.x < PARTS && part < B.nblk_c) {
+        double sv = 0.0;
+        for (int g = 0; g < VOL_GROUP; ++g) sv += vol[VOL_GROUP * threadIdx.x + g];
+        store_partials(P, B, part, &sv, 1);
+    }
 }
 
 // ---------------------------------------------------------------- vertex velocities
 // Fluid velocity at every membrane vertex from the moments of f^{n+1} (the tentative velocity
 // of Eq. verletPos).  It needs nothing from the probes, so its blocks ride in the probe launch
 // and the vertex kernel only gathers forces and moves the vertices.  One group per vertex.
-template <bool SOLO, int G>
+template <bool SOLO, int G, bool WIDE>
 __device__ void vertex_velocity_block(const Pools& P, int vb) {
-    constexpr int MLS_NODES = MlsLane<G>::N, MLS_PER_BLOCK = IB_BLOCK / G;
+    constexpr int N = MlsLane<G, WIDE>::N, PTS = IB_BLOCK / G;
     const int b = block_body<SOLO>(P, P.blk_body_u, vb);
     const BodyDev& B = body_of<SOLO>(P, b);
-    if (B.rigid) return;
-    const JobDev& J = body_job<SOLO>(P, B);
+    if (B.rigid || (B.rw2 >= MLS_COMPACT_RW2) != WIDE) return;
+    const JobDev J = body_job<SOLO>(P, B);
     const int grp = threadIdx.x / G, lane = threadIdx.x % G;
-    const int v = (vb - B.blk_u0) * MLS_PER_BLOCK + grp;
-    if (v >= B.nv) return;
-    const long long gv = B.v0 + v;
+    const bool live = (vb - B.blk_u0) * PTS + grp < B.nv;
+    const long long gv = B.v0 + (live ? (vb - B.blk_u0) * PTS + grp : B.nv - 1);
     int err = 0;
     double x[3];
     load3(P.x + 3 * gv, x);
     const WinDesc md = P.mdesc[b];
-    MlsLane<G> m;
-    float4 mom[MLS_NODES];
-    mls_setup<G>(J, x, B.rw2, lane, m, err);
-    mls_moments<G>(P, J, B, md, m, mom, err);
-    mls_solve<G>(m, B.wq, false, err);
-    const double u0 = group_dot<G>(m.phi, 1, mom, 1), u1 = group_dot<G>(m.phi, 1, mom, 2),
-                 u2 = group_dot<G>(m.phi, 1, mom, 3);
-    if (lane == 0) {
-        P.u0v[3 * gv] = u0;
-        P.u0v[3 * gv + 1] = u1;
-        P.u0v[3 * gv + 2] = u2;
+    MlsLane<G, WIDE> m;
+    unsigned idx[N];
+    float4 mom[N];
+    mls_locate<G, WIDE>(x, B.rw2, lane, m);
+    mls_index<G, WIDE>(J, md, m, idx, err);
+#pragma unroll
+    for (int s = 0; s < N; ++s) mom[s] = P.mwin[B.win_off + idx[s]];
+    mls_solve<G, WIDE, false>(m, B.wq, err);
+    double u[3];
+    for (int a = 0; a < 3; ++a) {
+        double q[N];
+#pragma unroll
+        for (int s = 0; s < N; ++s) q[s] = a == 0 ? mom[s].y : (a == 1 ? mom[s].z : mom[s].w);
+        u[a] = pdot<G, WIDE>(m.phi, q);
     }
-    if (err) atomicOr(P.flags + B.job, err);
+    if (live && lane < 3) P.u0v[3 * gv + lane] = lane == 0 ? u[0] : (lane == 1 ? u[1] : u[2]);
+    if (err && live) atomicOr(P.flags + B.job, err);
 }
 
 // ---------------------------------------------------------------- triangles (probes)
 // Group 2k evaluates the outer probe of triangle k of the block, group 2k+1 the inner one.
 // Blocks from nblk_tri on compute the vertex velocities instead.
-// Four waves per SIMD: the compiler fits the kernel in 128 VGPRs (the batched form with a 20 B
-// spill).  Batched launches are throughput-bound and gain the most; a lone body's launch gains
-// where its markers outnumber a round of the chip (256x128x256), and loses nothing below.
-template <bool SOLO, int G>
+// The stress enters only as tau . n: with v1..v3 the gradient rows of the shape functions,
+// [(grad u + grad u^T) n]_i = sum_k (n . v_k) u_i,k + v_i,k (u_k . n), so a probe needs four sums
+// over its nodes, rho - 1 and these three, not rho - 1 and the nine components of grad u.
+template <bool SOLO, int G, bool WIDE>
 __global__ void __launch_bounds__(IB_BLOCK, 4) k_triangles(Pools P, int nblk_tri) {
-    constexpr int MLS_NODES = MlsLane<G>::N, MLS_PER_BLOCK = IB_BLOCK / G, TRI_PER_BLOCK = MLS_PER_BLOCK / 2;
+    constexpr int N = MlsLane<G, WIDE>::N, PTS = IB_BLOCK / G, TRIS = PTS / 2;
     if ((int)blockIdx.x >= nblk_tri) {
-        vertex_velocity_block<SOLO, G>(P, blockIdx.x - nblk_tri);
+        vertex_velocity_block<SOLO, G, WIDE>(P, blockIdx.x - nblk_tri);
         return;
     }
     const int b = block_body<SOLO>(P, P.blk_body_t, blockIdx.x);
     const BodyDev& B = body_of<SOLO>(P, b);
-    const JobDev& J = body_job<SOLO>(P, B);
+    if ((B.rw2 >= MLS_COMPACT_RW2) != WIDE) return;   // the other form's launch
+    const JobDev J = body_job<SOLO>(P, B);   // copied before the first store: one round of scalar loads
     BodyState& S = P.bstate[b];
     const int grp = threadIdx.x / G, lane = threadIdx.x % G;
     const int blk = blockIdx.x - B.blk_t0;
     const int k = grp >> 1, side = grp & 1;
-    const int t = blk * TRI_PER_BLOCK + k;
-    __shared__ double probe[MLS_PER_BLOCK][10];
-    __shared__ double red[TRI_PER_BLOCK][6];
+    const bool live = blk * TRIS + k < B.nt;
+    const int t = live ? blk * TRIS + k : B.nt - 1;   // spare groups repeat the last triangle
     const WinDesc md = P.mdesc[b];
     int err = 0;
-    double cen[3] = {0, 0, 0}, N[3] = {0, 0, 0}, nrm[3] = {0, 0, 0}, A = 0.0;
-    if (t < B.nt) {
-        // centroid and normal at x^n, as the centroid kernel of this step computed them
-        const double* g = P.tgeo + 6 * (B.t0 + t);
-        for (int a = 0; a < 3; ++a) { cen[a] = g[a]; N[a] = g[3 + a]; }
-        const double ln = sqrt(dot3(N, N));
-        A = 0.5 * ln;
-        for (int a = 0; a < 3; ++a) nrm[a] = N[a] / ln;
-        const double sg = side == 0 ? 1.0 : -1.0;
-        const double xp[3] = {cen[0] + sg * B.probe * nrm[0], cen[1] + sg * B.probe * nrm[1],
-                              cen[2] + sg * B.probe * nrm[2]};
-        MlsLane<G> m;
-        mls_setup<G>(J, xp, B.rw2, lane, m, err);
-        float4 mom[MLS_NODES];
-        mls_moments<G>(P, J, B, md, m, mom, err);
-        mls_solve<G>(m, B.wq, true, err);
-        // interpolated rho - 1 and the gradient rows of u* (diffuse derivatives)
-        double v[10];
-        v[0] = group_dot<G>(m.phi, 1, mom, 0);
-        for (int j = 0; j < 3; ++j) {
-            v[1 + j] = group_dot<G>(&m.gr[0][j], 3, mom, 1);
-            v[4 + j] = group_dot<G>(&m.gr[0][j], 3, mom, 2);
-            v[7 + j] = group_dot<G>(&m.gr[0][j], 3, mom, 3);
-        }
-        if (lane == 0)
-            for (int i = 0; i < 10; ++i) probe[grp][i] = v[i];
+    // centroid and normal at x^n, as the centroid kernel of this step computed them
+    const double* g = P.tgeo + 6 * (B.t0 + t);
+    double cen[3], nn[3], nrm[3], xp[3];
+    for (int a = 0; a < 3; ++a) { cen[a] = g[a]; nn[a] = g[3 + a]; }
+    const double ln = sqrt(dot3(nn, nn));
+    const double sg = side == 0 ? B.probe : -B.probe;
+    for (int a = 0; a < 3; ++a) {
+        nrm[a] = nn[a] / ln;
+        xp[a] = cen[a] + sg * nrm[a];
     }
-    if (err) atomicOr(P.flags + B.job, err);
-    __syncthreads();
-    double Ft[3] = {0, 0, 0}, Mt[3] = {0, 0, 0};
-    if (t < B.nt && side == 0 && lane == 0) {
-        // p = c_s^2 rho, tau = rho nu (grad u + grad u^T); grad u [i][j] = probe[1 + 3 i + j]
-        const double* pp = probe[grp];
-        const double* pm = probe[grp + 1];
-        const double nu = J.nu;
-        const double rp = 1.0 + pp[0], rm = 1.0 + pm[0];
-        const double dp = (pp[0] - pm[0]) * (1.0 / 3.0);
-        for (int i = 0; i < 3; ++i) {
-            double tn = 0.0;
-            for (int j = 0; j < 3; ++j)
-                tn += (rp * nu * (pp[1 + 3 * i + j] + pp[1 + 3 * j + i]) -
-                       rm * nu * (pm[1 + 3 * i + j] + pm[1 + 3 * j + i])) * nrm[j];
-            Ft[i] = (-dp * nrm[i] + tn) * A;
-        }
+    MlsLane<G, WIDE> m;
+    unsigned idx[N];
+    float4 mom[N];
+    mls_locate<G, WIDE>(xp, B.rw2, lane, m);
+    mls_index<G, WIDE>(J, md, m, idx, err);
+#pragma unroll
+    for (int s = 0; s < N; ++s) mom[s] = P.mwin[B.win_off + idx[s]];
+    double gr[N][3], gn[N], one[N];
+    mls_solve<G, WIDE, true>(m, B.wq, err, nrm, gr, gn);
+    double q[N], un[N], T[3];
+#pragma unroll
+    for (int s = 0; s < N; ++s) {
+        q[s] = mom[s].x;
+        un[s] = fma((double)mom[s].w, nrm[2], fma((double)mom[s].z, nrm[1], (double)mom[s].y * nrm[0]));
+        one[s] = 1.0;
+    }
+    const double r = pdot<G, WIDE>(m.phi, q);   // rho - 1 at the probe
+    for (int i = 0; i < 3; ++i) {
+#pragma unroll
+        for (int s = 0; s < N; ++s)
+            q[s] = fma(gr[s][i], un[s], gn[s] * (double)(i == 0 ? mom[s].y : (i == 1 ? mom[s].z : mom[s].w)));
+        T[i] = pdot<G, WIDE>(one, q);
+    }
+    if (err && live) atomicOr(P.flags + B.job, err);
+    // outer minus inner probe: p = c_s^2 rho, tau = rho nu (grad u + grad u^T)
+    const double nu = J.nu, v = (1.0 + r) * nu;
+    auto other = [](double x) { return G == 8 ? dpp_f64<0x128>(x) : dpp_f64<0x141>(x); };   // row_ror:8, row_half_mirror
+    const double dp = (r - other(r)) * (1.0 / 3.0);
+    double Ft[3], Mt[3] = {0, 0, 0};
+    for (int i = 0; i < 3; ++i) {
+        const double f = v * T[i];
+        Ft[i] = (f - other(f) - dp * nrm[i]) * (0.5 * ln);
+    }
+    const bool store = live && side == 0 && lane == 0;
+    if (store)
         for (int i = 0; i < 3; ++i) P.fext[3 * (B.t0 + t) + i] = Ft[i];
-        if (!B.rigid) {
-            // volume penalty (Eq. volFor, restoring): k_v (1 - V/V0) n_t A_t, a third per vertex
-            const double vs = B.kv == 0.0 ? 0.0 : B.kv * (1.0 - S.V / B.V0) * (1.0 / 6.0);
-            for (int i = 0; i < 3; ++i) P.fvol[3 * (B.t0 + t) + i] = vs * N[i];
-        } else {
-            const double rr[3] = {cen[0] - S.X[0], cen[1] - S.X[1], cen[2] - S.X[2]};
-            cross3(rr, Ft, Mt);
-        }
+    if (!B.rigid) {
+        // volume penalty (Eq. volFor, restoring): k_v (1 - V/V0) n_t A_t, a third per vertex
+        const double vs = B.kv == 0.0 ? 0.0 : B.kv * (1.0 - S.V / B.V0) * (1.0 / 6.0);
+        if (store)
+            for (int i = 0; i < 3; ++i) P.fvol[3 * (B.t0 + t) + i] = vs * nn[i];
+        return;
     }
-    if (!B.rigid) return;
+    // one partial of force and torque per RED_GROUP triangles, folded, with the pose update, by
+    // k_fold_bodies
+    __shared__ double red[TRIS][6];
+    const double rr[3] = {cen[0] - S.X[0], cen[1] - S.X[1], cen[2] - S.X[2]};
+    cross3(rr, Ft, Mt);
     if (side == 0 && lane == 0)
-        for (int i = 0; i < 3; ++i) { red[k][i] = Ft[i]; red[k][3 + i] = Mt[i]; }
+        for (int i = 0; i < 3; ++i) { red[k][i] = live ? Ft[i] : 0.0; red[k][3 + i] = live ? Mt[i] : 0.0; }
     __syncthreads();
-    if (threadIdx.x != 0) return;
-    double part[6] = {0, 0, 0, 0, 0, 0};
-    for (int g = 0; g < TRI_PER_BLOCK; ++g)
-        for (int i = 0; i < 6; ++i) part[i] += red[g][i];
-    store_partials(P, B, blk, part, 6);   // folded, with the pose update, by k_fold_bodies
+    constexpr int PARTS = TRIS / RED_GROUP;
+    const int part = (int)threadIdx.x / 8, i = threadIdx.x % 8;
+    if (part < PARTS && i < 6 && blk * PARTS + part < B.nblk_t) {
+        double sum = 0.0;
+        for (int q4 = 0; q4 < RED_GROUP; ++q4) sum += red[RED_GROUP * part + q4][i];
+        P.partial[16LL * B.red_slot + i * partial_stride(B) + blk * PARTS + part] = sum;
+    }
 }
 
 // Rigid body, Eqs. (linearVelRig), (angularVelRig), from the FP64 totals tot = (F, M).  Returns
@@ -819,7 +904,6 @@ template <bool SOLO>
 __global__ void __launch_bounds__(VERT_BLOCK) k_vertices(Pools P) {
     const int b = block_body<SOLO>(P, P.blk_body_v, blockIdx.x);
     const BodyDev& B = body_of<SOLO>(P, b);
-    const JobDev& J = body_job<SOLO>(P, B);
     BodyState& S = P.bstate[b];
     const int grp = threadIdx.x / VERT_GROUP, lane = threadIdx.x % VERT_GROUP;
     const int blk = blockIdx.x - B.blk_v0;
@@ -1005,11 +1089,18 @@ __global__ void __launch_bounds__(256) k_body_totals(Pools P, int b, double* out
     if (t < 6) out[t] = red[t][0];
 }
 
-void launch_centroids(const Pools& P, int nblk_tri, int nblk_edge, bool fold, hipStream_t s) {
+// A launch in the compact form and, where a body's support needs it, one in the WIDE form: each
+// serves the bodies of its form.  The edge blocks ride in the first.
+void launch_centroids(const Pools& P, int nblk_tri, int nblk_edge, bool fold, bool wide, hipStream_t s) {
     if (!(nblk_tri + nblk_edge > 0)) return;
     const dim3 grid(nblk_tri + nblk_edge), block(IB_BLOCK);
-    if (P.solo_job >= 0) hipLaunchKernelGGL((k_centroids<true, MLS_GROUP>), grid, block, 0, s, P, nblk_tri, (int)fold);
-    else hipLaunchKernelGGL((k_centroids<false, MLS_GROUP>), grid, block, 0, s, P, nblk_tri, (int)fold);
+    if (P.solo_job >= 0) {
+        hipLaunchKernelGGL((k_centroids<true, 8, false>), grid, block, 0, s, P, nblk_tri, (int)fold);
+        if (wide) hipLaunchKernelGGL((k_centroids<true, 8, true>), dim3(nblk_tri), block, 0, s, P, nblk_tri, (int)fold);
+    } else {
+        hipLaunchKernelGGL((k_centroids<false, 8, false>), grid, block, 0, s, P, nblk_tri, (int)fold);
+        if (wide) hipLaunchKernelGGL((k_centroids<false, 8, true>), dim3(nblk_tri), block, 0, s, P, nblk_tri, (int)fold);
+    }
 }
 void launch_windows(const Pools& P, int nbodies, hipStream_t s) {
     if (nbodies > 0) hipLaunchKernelGGL(k_windows, dim3(nbodies), dim3(256), 0, s, P);
@@ -1018,11 +1109,16 @@ void launch_fold_bodies(const Pools& P, int nbodies, int mode, hipStream_t s) {
     if (nbodies > 0) hipLaunchKernelGGL(k_fold_bodies, dim3(nbodies), dim3(FOLD_THREADS), 0, s, P, mode);
 }
 
-void launch_triangles(const Pools& P, int nblk_tri, int nblk_vel, hipStream_t s) {
+void launch_triangles(const Pools& P, int nblk_tri, int nblk_vel, bool wide, hipStream_t s) {
     if (!(nblk_tri + nblk_vel > 0)) return;
     const dim3 grid(nblk_tri + nblk_vel), block(IB_BLOCK);
-    if (P.solo_job >= 0) hipLaunchKernelGGL((k_triangles<true, MLS_GROUP>), grid, block, 0, s, P, nblk_tri);
-    else hipLaunchKernelGGL((k_triangles<false, MLS_GROUP>), grid, block, 0, s, P, nblk_tri);
+    if (P.solo_job >= 0) {
+        hipLaunchKernelGGL((k_triangles<true, 8, false>), grid, block, 0, s, P, nblk_tri);
+        if (wide) hipLaunchKernelGGL((k_triangles<true, 8, true>), grid, block, 0, s, P, nblk_tri);
+    } else {
+        hipLaunchKernelGGL((k_triangles<false, 8, false>), grid, block, 0, s, P, nblk_tri);
+        if (wide) hipLaunchKernelGGL((k_triangles<false, 8, true>), grid, block, 0, s, P, nblk_tri);
+    }
 }
 void launch_vertices(const Pools& P, int nblocks, hipStream_t s) {
     if (!(nblocks > 0)) return;

@@ -20,20 +20,22 @@ constexpr double FIX_SCALE = 1099511627776.0;  // 2^40
 constexpr double FIX_INV = 1.0 / 1099511627776.0;
 constexpr int WIN_MARGIN = 4;    // nodes around a body's bounding box (probe + support + slack)
 constexpr int IB_BLOCK = 64;      // threads per block of the marker kernels: one wave
-// lanes that evaluate one MLS point (four stencil nodes each), MLS points per block, and
-// triangles per probe block (two points, the +/- probes, per triangle)
+// lanes that evaluate one MLS point, MLS points per block, and triangles per probe block (two
+// points, the +/- probes, per triangle)
 constexpr int MLS_GROUP = 8;
 constexpr int MLS_PER_BLOCK = IB_BLOCK / MLS_GROUP;
 constexpr int TRI_PER_BLOCK = MLS_PER_BLOCK / 2;
+// triangles per partial sum of the enclosed volume, and of a rigid body's force and torque
+constexpr int VOL_GROUP = MLS_PER_BLOCK;
+constexpr int RED_GROUP = TRI_PER_BLOCK;
 // the vertex kernel gathers each vertex's incident forces with 16 lanes (one DPP row), 16
 // vertices per block (the centroid blocks fold one box per vertex block into the force window)
 constexpr int VERT_GROUP = 16;
 constexpr int VERT_BLOCK = 256;
 constexpr int VERT_PER_BLOCK = VERT_BLOCK / VERT_GROUP;
 constexpr int MAX_RED_BLOCKS = 65536;
-// window-moments blocks of a membrane: one 256-thread block per this many nodes of the window it
-// usually spans (rigid bodies: one per 256 nodes, see win_blocks)
-constexpr int WIN_NODES_PER_BLOCK = 2048;
+// squared support radius from which an MLS point takes the form with all 27 nodes around it
+constexpr double MLS_COMPACT_RW2 = 1.9;
 
 // error flag bits (per job)
 constexpr int FLAG_DOMAIN = 1;     // a support or probe reached a wall node / left the domain
@@ -86,7 +88,7 @@ struct JobDev {
     float omega;          // 1 / tau
     float guo;            // 1 - 1/(2 tau)
     float nu;             // (tau - 1/2) / 3
-    int zh_axes;          // axes carrying Zou-He walls (more than one: edge and corner closure)
+    unsigned walls;       // bit f (lbib_bc face order): face f is not periodic; WALL_TERMS
     int bc[6];
     float wall_u[6][3];
     float G[3];           // uniform body force density
@@ -96,9 +98,15 @@ struct JobDev {
     unsigned mx, my;
 };
 
+// Bit of JobDev::walls set when some wall adds a term to the redirected populations (a moving
+// bounce-back wall, or a Zou-He wall whose unknowns are rebuilt).  Halfway bounce-back at rest is the
+// redirect alone.
+constexpr unsigned WALL_TERMS = 64u;
+
 struct WinDesc {
     int o[3];  // origin node (0 <= o < n along periodic axes)
     int w[3];  // extent
+    int b[3];  // origin in the body's unwrapped coordinates (differs from o by whole periods)
 };
 
 // A window is usable when 0 <= o < n and 1 <= w <= min(n, cap) on every axis, and on walled
@@ -210,6 +218,12 @@ __device__ __forceinline__ const JobDev& body_job(const Pools& P, const BodyDev&
     return P.jobs[SOLO ? P.solo_job : B.job];
 }
 
+// Make a value loaded from a table available here, in scalar registers.  Uniform loads otherwise
+// stay behind the branches before their uses, one dependent round trip beyond the L2 each, which is
+// what short launches spend their time on.
+template <typename... T>
+__device__ __forceinline__ void loaded(T&... v) { (..., [](auto& x) { asm volatile("" : "+s"(x)); }(v)); }
+
 // ---------------------------------------------------------------- launchers
 struct SweepShape {
     int block;          // threads per block
@@ -249,11 +263,12 @@ void launch_init_eq(const Pools& P, int storage, bool to_b, int job, long long n
 // lbib_ib.hip
 // fold: the centroid blocks derive this step's force window from the vertex-block boxes
 // themselves; otherwise launch_windows after the vertex kernel has published it.
-void launch_centroids(const Pools& P, int nblk_tri, int nblk_edge, bool fold, hipStream_t s);
+// wide: some body's MLS support needs all 27 nodes around a point.
+void launch_centroids(const Pools& P, int nblk_tri, int nblk_edge, bool fold, bool wide, hipStream_t s);
 void launch_windows(const Pools& P, int nbodies, hipStream_t s);
 // bodies from which the force windows are folded once per body by a kernel of their own
 constexpr int WINDOW_KERNEL_MIN_BODIES = 2;
-void launch_triangles(const Pools& P, int nblk_tri, int nblk_vel, hipStream_t s);
+void launch_triangles(const Pools& P, int nblk_tri, int nblk_vel, bool wide, hipStream_t s);
 // mode 0: volumes of membranes with a volume penalty; mode 1: rigid totals and pose update
 void launch_fold_bodies(const Pools& P, int nbodies, int mode, hipStream_t s);
 void launch_vertices(const Pools& P, int nblocks, hipStream_t s);

@@ -299,21 +299,6 @@ __device__ __forceinline__ void zou_he_corner(const JobDev& J, int s0, int s1, i
 }
 
 // ---------------------------------------------------------------- pull
-// Walls of job J: bit f (lbib_bc face order) set for a face that is not periodic; WALL_TERMS set
-// when some wall adds a term to the redirected populations (a moving bounce-back wall, or a
-// Zou-He wall whose unknowns are rebuilt).  Halfway bounce-back at rest is the redirect alone.
-constexpr unsigned WALL_TERMS = 64u;
-__device__ __forceinline__ unsigned wall_faces(const JobDev& J) {
-    unsigned m = 0;
-#pragma unroll
-    for (int f = 0; f < 6; ++f) {
-        m |= (J.bc[f] != 0 ? 1u : 0u) << f;
-        const bool moving = J.wall_u[f][0] != 0.f || J.wall_u[f][1] != 0.f || J.wall_u[f][2] != 0.f;
-        if (J.bc[f] == 1 || (J.bc[f] == 2 && moving)) m |= WALL_TERMS;
-    }
-    return m;
-}
-
 // Post-streaming deviations at node (x, y, z) of job J from the post-collision buffer src.
 // All 19 loads are issued unconditionally, so they are in flight together: a source outside
 // the domain is redirected to the node's own opposite population (the halfway bounce-back
@@ -705,7 +690,7 @@ __global__ void __launch_bounds__(1024) k_sweep(Pools P, int a_to_b, int xcd_chu
         W = load_win1(P, J);
     }
     const unsigned nx = (unsigned)J.nx, ny = (unsigned)J.ny, mx = J.mx, my = J.my;
-    const unsigned walls = wall_faces(J);
+    const unsigned walls = J.walls;
     // the job's step counter of the buffer being read seeds the stochastic narrowing; the block of
     // the job's first tile hands the next value to the other buffer's slot, read by the next step
     unsigned seed = 0;
@@ -779,27 +764,35 @@ void launch_sweep(const Pools& P, int storage, bool collide, bool a_to_b, int nt
 // ---------------------------------------------------------------- window moments
 // For every node of a body's current window: pull the post-streaming state, store
 // (rho - 1, u*) with u* = sum f e / rho, and clear the force window for the next step.
+// A lone body's launch is one chain of dependent reads (arguments, job and layout, populations) with
+// about a node per thread: the job record is copied before the first store, which the compiler must
+// otherwise assume to change it, so all of it arrives in one round of scalar loads.
 template <typename S, bool SOLO>
 __global__ void __launch_bounds__(256) k_window_moments(Pools P, int from_b) {
-    // blocks of a body are proportional to its window capacity; they stride over the current
-    // window, which is usually far smaller than the capacity
+    // blocks of a body are proportional to its window at rest; they stride over the current one
     const int b = block_body<SOLO>(P, P.blk_body_w, blockIdx.x);
     const BodyDev& B = body_of<SOLO>(P, b);
-    const JobDev& J = body_job<SOLO>(P, B);
-    const int lb = blockIdx.x - B.blk_w0;
-    const WinDesc d = P.fdesc[b];
+    JobDev J = body_job<SOLO>(P, B);
+    WinDesc d;
+    for (int a = 0; a < 3; ++a) { d.o[a] = P.fdesc[b].o[a]; d.w[a] = P.fdesc[b].w[a]; }
+    int nblk = B.nblk_w, lb = blockIdx.x - B.blk_w0, cap[3] = {B.win_cap[0], B.win_cap[1], B.win_cap[2]};
+    long long off = B.win_off;
+    void* pop = from_b ? P.popB : P.popA;
+    float4* mwin = P.mwin;
+    long long* fwin = P.fwin;
+    loaded(J.nx, J.ny, J.nz, J.n, J.pop_off, J.walls, J.bc[0], J.bc[2], J.bc[4], J.wall_u[0][0], J.wall_u[2][0],
+           J.wall_u[5][2], d.o[0], d.w[0], d.w[1], d.w[2], nblk, lb, cap[0], off, pop, mwin, fwin);
+    const unsigned stride = (unsigned)nblk * blockDim.x;
+    const long long capn = (long long)cap[0] * cap[1] * cap[2];
     const int dims[3] = {J.nx, J.ny, J.nz};
-    if (!win_valid(d, dims, B.win_cap, J.bc)) {
+    if (!win_valid(d, dims, cap, J.bc)) {
         if (lb == 0 && threadIdx.x == 0) atomicOr(P.flags + B.job, FLAG_WINDOW);
         return;
     }
-    if (lb == 0 && threadIdx.x == 0) P.mdesc[b] = d;
     // window sizes are bounded by the capacity, far below 2^31 nodes: 32-bit index arithmetic
     const unsigned nw = (unsigned)d.w[0] * d.w[1] * d.w[2];
     const unsigned w0 = d.w[0], w01 = (unsigned)d.w[0] * d.w[1];
-    const long long capn = (long long)B.win_cap[0] * B.win_cap[1] * B.win_cap[2];
-    const S* src = (const S*)(from_b ? P.popB : P.popA) + J.pop_off;
-    const unsigned stride = (unsigned)B.nblk_w * blockDim.x;
+    const S* src = (const S*)pop + J.pop_off;
     for (unsigned l = (unsigned)lb * blockDim.x + threadIdx.x; l < nw; l += stride) {
         const unsigned lz = l / w01, rem = l - lz * w01;
         const unsigned ly = rem / w0, lx = rem - ly * w0;
@@ -811,7 +804,7 @@ __global__ void __launch_bounds__(256) k_window_moments(Pools P, int from_b) {
         // MLS supports exclude Zou-He wall nodes (their moments are never read), so the pull
         // skips the Zou-He closure here
         float g[Q];
-        pull<S, false>(src, J, x, y, z, k, g, wall_faces(J));
+        pull<S, false>(src, J, x, y, z, k, g, J.walls);
         float drho = 0.f, jx = 0.f, jy = 0.f, jz = 0.f;
 #pragma unroll
         for (int i = 0; i < Q; ++i) {
@@ -821,12 +814,13 @@ __global__ void __launch_bounds__(256) k_window_moments(Pools P, int from_b) {
             jz += cz(i) * g[i];
         }
         const float ir = 1.f / (1.f + drho);
-        P.mwin[B.win_off + l] = make_float4(drho, jx * ir, jy * ir, jz * ir);
-        long long* fw = P.fwin + 3 * B.win_off + l;
+        mwin[off + l] = make_float4(drho, jx * ir, jy * ir, jz * ir);
+        long long* fw = fwin + 3 * off + l;
         fw[0] = 0;
         fw[capn] = 0;
         fw[2 * capn] = 0;
     }
+    if (lb == 0 && threadIdx.x == 0) P.mdesc[b] = P.fdesc[b];
 }
 
 void launch_window_moments(const Pools& P, int storage, bool from_b, int nblk_w, hipStream_t s) {
@@ -854,7 +848,7 @@ __device__ __forceinline__ float4 node_moments(const Pools& P, const JobDev& J, 
     node_coords(J, k, x, y, z);
     const S* src = (const S*)(from_b ? P.popB : P.popA) + J.pop_off;
     float g[Q];
-    pull<S>(src, J, x, y, z, k, g, wall_faces(J));
+    pull<S>(src, J, x, y, z, k, g, J.walls);
     float drho = 0.f, jx = 0.f, jy = 0.f, jz = 0.f;
 #pragma unroll
     for (int i = 0; i < Q; ++i) {
@@ -900,7 +894,7 @@ __global__ void k_get_pop_plane(Pools P, int from_b, int job, int plane, double*
     node_coords(J, k, x, y, z);
     const S* src = (const S*)(from_b ? P.popB : P.popA) + J.pop_off;
     float g[Q];
-    pull<S>(src, J, x, y, z, k, g, wall_faces(J));
+    pull<S>(src, J, x, y, z, k, g, J.walls);
     float gi = g[0];
 #pragma unroll
     for (int i = 1; i < Q; ++i)

@@ -22,18 +22,13 @@ constexpr int WS_MAX_VALENCE = 12;
 size_t workspace_need(const lbib_lattice_desc& d, long long nv, long long nt);
 // Force-window capacity per axis for a body of bounding radius rbound about its vertex mean.
 void window_capacity(const int dims[3], bool rigid, double rbound, int cap[3]);
-// Window-moments blocks of such a body (its B.nblk_w).
-long long window_blocks(const int dims[3], bool rigid, double rbound);
-// Window-moments blocks for a window of capn nodes.  A rigid body's window stays at its
-// capacity (the box only moves), so it gets one 256-thread block per 256 nodes, a node per thread.
-// A membrane gets one block per WIN_NODES_PER_BLOCK nodes of the window it usually spans (2.5
-// times its rest extent per axis), about fifteen times the volume of its current window, so each
-// thread still has about one node of it; the blocks stride over larger windows.
-constexpr int WIN_NODES_PER_BLOCK_RIGID = 256;
-inline long long win_blocks(long long capn, bool rigid) {
-    const long long per = rigid ? WIN_NODES_PER_BLOCK_RIGID : WIN_NODES_PER_BLOCK;
-    return capn > per ? (capn + per - 1) / per : 1;
-}
+// Window-moments blocks of a body of bounding radius rbound (its B.nblk_w): one 256-thread block per
+// 256 nodes of the window it spans at rest, a node per thread.  With a block per 2048 nodes of 2.5
+// times the rest extent, as membranes had before, the 32^3 capsule's 10,600 nodes were walked by
+// 4,096 threads, three dependent rounds of loads each.
+constexpr int WIN_NODES_PER_BLOCK = 256;
+long long window_blocks(const int dims[3], double rbound);
+inline long long win_blocks(long long capn) { return (capn + WIN_NODES_PER_BLOCK - 1) / WIN_NODES_PER_BLOCK; }
 
 // Device memory: a caller workspace carved by a bump pointer, or hipMalloc'd blocks.
 struct Arena {
@@ -99,6 +94,7 @@ struct Batch {
     int nbodies = 0;
     int nblk_c = 0, nblk_e = 0, nblk_t = 0, nblk_v = 0, nblk_u = 0, nblk_w = 0;
     bool any_rigid = false, any_volume = false;   // bodies needing the per-body fold launches
+    bool any_wide = false;   // a body whose MLS support needs all 27 nodes around a point
     Pools P{};
     bool cur_b = false;        // buffer holding the latest post-collision state
     bool primed = false;       // moment windows hold the moments of the current state

@@ -133,7 +133,7 @@ size_t workspace_need(const lbib_lattice_desc& d, long long nv, long long nt) {
     const long long nbu = (nv + MLS_PER_BLOCK - 1) / MLS_PER_BLOCK;
     const long long nbv = (nv + VERT_PER_BLOCK - 1) / VERT_PER_BLOCK, nbe = (ne + IB_BLOCK - 1) / IB_BLOCK;
     const long long capn = body ? n : 0;
-    const long long nbw = body ? win_blocks(capn, true) : 0;   // the larger, rigid count
+    const long long nbw = body ? win_blocks(capn) : 0;
     b += r(sizeof(BodyDev)) + r(4 * nbc) + r(4 * nbe) + r(4 * nbt) + r(4 * nbv) + r(4 * nbu) + r(4 * nbw);
     b += 6 * r(24 * nv);                                             // x, xprev, uv, fv, u0v, xb
     b += r(12 * nt) + r(8 * ne) + r(16 * ne) + 3 * r(8 * ne);        // tri, edge, hinge, l0, ks, theta0
@@ -154,14 +154,13 @@ void window_capacity(const int dims[3], bool rigid, double rbound, int cap[3]) {
         cap[a] = rigid ? std::min(dims[a], (int)std::ceil(2.0 * rbound) + 2 * WIN_MARGIN + 4) : dims[a];
 }
 
-long long window_blocks(const int dims[3], bool rigid, double rbound) {
-    // the window a membrane usually spans: 2.5 times its rest extent per axis (a Taylor
-    // deformation near 0.6 at fixed volume); larger windows are covered by the same blocks
-    const double grow = rigid ? 1.0 : 2.5;
+long long window_blocks(const int dims[3], double rbound) {
+    // the window a body spans at rest, in any orientation, with some nodes of growth; a membrane
+    // that stretches further is covered by the same blocks
     long long n = 1;
     for (int a = 0; a < 3; ++a)
-        n *= std::min(dims[a], (int)std::ceil(2.0 * grow * rbound) + 2 * WIN_MARGIN + 4);
-    return win_blocks(n, rigid);
+        n *= std::min(dims[a], (int)std::ceil(2.0 * rbound) + 2 * WIN_MARGIN + 4);
+    return win_blocks(n);
 }
 
 // ---------------------------------------------------------------- body rest state
@@ -355,12 +354,14 @@ static WinDesc window_for(const JobDev& J, const double lo[3], const double hi[3
         int l = (int)std::floor(lo[a]) - WIN_MARGIN, h = (int)std::ceil(hi[a]) + WIN_MARGIN;
         if (J.bc[2 * a] == 0) {
             const int w = h - l + 1;
-            if (w >= dims[a]) { d.o[a] = 0; d.w[a] = dims[a]; }
-            else { int o = l % dims[a]; if (o < 0) o += dims[a]; d.o[a] = o; d.w[a] = w; }
+            int o = l % dims[a];
+            if (o < 0) o += dims[a];
+            if (w >= dims[a]) { d.o[a] = 0; d.w[a] = dims[a]; d.b[a] = l - o; }
+            else { d.o[a] = o; d.w[a] = w; d.b[a] = l; }
         } else {
             l = std::max(l, 0);
             h = std::min(h, dims[a] - 1);
-            d.o[a] = l;
+            d.o[a] = d.b[a] = l;
             d.w[a] = h >= l ? h - l + 1 : 1;
         }
         if (d.w[a] > cap[a]) { *over = true; d.w[a] = cap[a]; }
@@ -397,8 +398,11 @@ void Batch::job_from_desc(const lbib_lattice_desc& d, JobDev& J) {
         J.bc[f] = d.bc[f];
         for (int a = 0; a < 3; ++a) J.wall_u[f][a] = (float)d.wall_u[f][a];
     }
-    for (int a = 0; a < 3; ++a)
-        if (d.bc[2 * a] == 1 || d.bc[2 * a + 1] == 1) ++J.zh_axes;
+    for (int f = 0; f < 6; ++f) {
+        J.walls |= (d.bc[f] != 0 ? 1u : 0u) << f;
+        const bool moving = J.wall_u[f][0] != 0.f || J.wall_u[f][1] != 0.f || J.wall_u[f][2] != 0.f;
+        if (d.bc[f] == 1 || (d.bc[f] == 2 && moving)) J.walls |= WALL_TERMS;
+    }
     for (int a = 0; a < 3; ++a) J.G[a] = (float)d.body_force[a];
     J.mx = d.nx < (1 << 15) ? (unsigned)((0x100000000ULL + d.nx - 1) / d.nx) : 0u;
     J.my = d.ny < (1 << 15) ? (unsigned)((0x100000000ULL + d.ny - 1) / d.ny) : 0u;
@@ -506,7 +510,7 @@ void body_record(const HostBody& h, const JobDev& J, BodyDev& B) {
     for (int k = 0; k < 9; ++k) B.Ib[k] = h.Ib[k];
     const int dims[3] = {J.nx, J.ny, J.nz};
     window_capacity(dims, h.desc.rigid != 0, h.rbound, B.win_cap);
-    B.nblk_w = (int)window_blocks(dims, h.desc.rigid != 0, h.rbound);
+    B.nblk_w = (int)window_blocks(dims, h.rbound);
 }
 
 // Append body h's incidence lists padded to widths wt (triangles) and wh (hinge roles), -1 past
@@ -610,8 +614,9 @@ lbib_status Batch::rebuild_bodies() {
     nbodies = (int)hbodies.size();
     P.solo_job = nbodies == 1 ? hbodies[0].job : -1;
     if (nbodies == 1) P.solo_body = bd[0];
-    any_rigid = any_volume = false;
+    any_rigid = any_volume = any_wide = false;
     for (const HostBody& h : hbodies) {
+        if (h.desc.mls_rw * h.desc.mls_rw >= MLS_COMPACT_RW2) any_wide = true;
         if (h.desc.rigid) any_rigid = true;
         else if (h.desc.kv != 0.0) any_volume = true;
     }
@@ -823,7 +828,7 @@ lbib_status Batch::enqueue_step(bool collide) {
     const bool bodies = collide && nbodies > 0;
     const bool fold_once = nbodies >= WINDOW_KERNEL_MIN_BODIES;
     if (bodies) {
-        launch_centroids(P, nblk_c, nblk_e, !fold_once, stream);
+        launch_centroids(P, nblk_c, nblk_e, !fold_once, any_wide, stream);
         if (any_volume) launch_fold_bodies(P, nbodies, 0, stream);
     }
     if (timing && sweep_seq++ % timing_period == 0) {
@@ -839,7 +844,7 @@ lbib_status Batch::enqueue_step(bool collide) {
     cur_b = !cur_b;
     if (bodies) {
         launch_window_moments(P, storage, cur_b, nblk_w, stream);
-        launch_triangles(P, nblk_t, nblk_u, stream);
+        launch_triangles(P, nblk_t, nblk_u, any_wide, stream);
         if (any_rigid) launch_fold_bodies(P, nbodies, 1, stream);
         launch_vertices(P, nblk_v, stream);
         if (fold_once) launch_windows(P, nbodies, stream);
@@ -1023,7 +1028,7 @@ uint64_t slot_device_bytes(const SlotCaps& c, int storage) {
     const uint64_t bc = (nt + MLS_PER_BLOCK - 1) / MLS_PER_BLOCK, bt = (nt + TRI_PER_BLOCK - 1) / TRI_PER_BLOCK;
     const uint64_t bu = (nv + MLS_PER_BLOCK - 1) / MLS_PER_BLOCK, bv = (nv + VERT_PER_BLOCK - 1) / VERT_PER_BLOCK;
     const uint64_t be = (ne + IB_BLOCK - 1) / IB_BLOCK;
-    const uint64_t bw = (uint64_t)win_blocks((long long)win, true);
+    const uint64_t bw = (uint64_t)win_blocks((long long)win);
     uint64_t b = 2 * 19 * nodes * es + 4 + 8 + sizeof(JobDev) + sizeof(int4) * ((nodes + per - 1) / per);
     b += sizeof(BodyDev) + 4 * (bc + be + bt + bv + bu + bw);
     b += 6 * 24 * nv + 12 * nt + 8 * ne + 16 * ne + 3 * 8 * ne;
@@ -1051,7 +1056,7 @@ lbib_status Batch::create_slotted(int nslots, const SlotCaps& c, int storage_, v
     bt_slot = (c.nt + TRI_PER_BLOCK - 1) / TRI_PER_BLOCK;
     bu_slot = (c.nv + MLS_PER_BLOCK - 1) / MLS_PER_BLOCK;
     bv_slot = (c.nv + VERT_PER_BLOCK - 1) / VERT_PER_BLOCK;
-    bw_slot = (int)win_blocks(win_slot, true);
+    bw_slot = (int)win_blocks(win_slot);
     red_slot = std::max(bc_slot, bt_slot);
     const long long S = nslots;
     // lattices: empty slots hold no job (n = 0)
@@ -1165,6 +1170,7 @@ lbib_status Batch::slot_tables() {
     const int S = (int)slot_live.size();
     const long long per = (long long)shape.block * shape.npt;
     tiles.clear();
+    any_wide = false;
     std::vector<int> bc, be, bt, bv, bu, bw;
     for (int s = 0; s < S; ++s) {
         JobDev& J = jobs[s];
@@ -1180,6 +1186,7 @@ lbib_status Batch::slot_tables() {
             tiles.push_back(make_int4(s, (int)(k0 - q * J.nx), (int)(q % J.ny), (int)(q / J.ny)));
         }
         if (B.nv == 0) continue;
+        if (B.rw2 >= MLS_COMPACT_RW2) any_wide = true;
         const int nbc = (B.nt + MLS_PER_BLOCK - 1) / MLS_PER_BLOCK, nbt = (B.nt + TRI_PER_BLOCK - 1) / TRI_PER_BLOCK;
         const int nbu = (B.nv + MLS_PER_BLOCK - 1) / MLS_PER_BLOCK, nbv = (B.nv + VERT_PER_BLOCK - 1) / VERT_PER_BLOCK;
         const int nbe = B.rigid ? 0 : (B.ne + IB_BLOCK - 1) / IB_BLOCK;

@@ -1,0 +1,108 @@
+"""The moving-least-squares form with 16 candidate nodes per point, against the rule it rests on
+(CPU) and against the FP64 oracle at the support radii, positions and windows where its choice of
+nodes or its index arithmetic could go wrong."""
+import itertools
+import os
+
+import numpy as np
+import pytest
+
+from paper_2207_06029_amd import inputs as I
+
+
+def _candidates(f):
+    """The 8 corners of the cell around the point and the 7 far nodes; f = |x - nearest| per axis,
+    the point on the + side of its nearest node."""
+    near, second, far = 0, 1, -1
+    out = set(itertools.product((near, second), repeat=3))
+    for axes in itertools.chain.from_iterable(itertools.combinations(range(3), n) for n in (1, 2, 3)):
+        node = [near] * 3
+        for a in axes:
+            node[a] = second
+        node[min(axes, key=lambda a: f[a])] = far
+        out.add(tuple(node))
+    return out
+
+
+@pytest.mark.parametrize("rw", [0.9, 1.3, 1.378])
+def test_candidates_hold_every_support_node(rw):
+    rng = np.random.default_rng(11)
+    pts = np.concatenate([rng.uniform(0.0, 0.5, (4000, 3)), rng.choice([0.0, 0.17, 0.25, 0.3, 0.5], (500, 3))])
+    block = list(itertools.product((-1, 0, 1), repeat=3))
+    for f in pts:
+        cand = _candidates(f)
+        assert len(cand) == 15
+        for n in block:
+            if sum((n[a] - f[a]) ** 2 for a in range(3)) <= rw * rw:
+                assert n in cand
+
+
+@pytest.fixture(scope="module")
+def api():
+    from paper_2207_06029_amd import api as A
+    return A
+
+
+CASES = {
+    # compact form: the usual radius, the largest below the bound, a point set on lattice symmetries
+    "rw1.3": dict(rw=1.3),
+    "rw1.378": dict(rw=1.378),
+    "on nodes": dict(rw=1.3, centre=(12.0, 12.0, 12.0)),
+    # the form with all 27 nodes
+    "rw1.379": dict(rw=1.379),
+    "rw1.49": dict(rw=1.49),
+    # a window across a periodic face, and one that spans the lattice, left by a whole period
+    "wrapped": dict(rw=1.3, centre=(0.3, 12.1, 23.4)),
+    "spanning": dict(rw=1.3, dims=(12, 24, 12), centre=(29.7, 11.5, -18.2)),
+    "wide spanning": dict(rw=1.45, dims=(12, 24, 12), centre=(5.7, 11.5, 6.2)),
+    # a window clipped by the walls, and a coarse mesh whose stencil box exceeds the on-chip one
+    "clipped": dict(rw=1.3, dims=(24, 15, 24), centre=(11.5, 7.0, 11.5), radius=3.4),
+    "coarse": dict(rw=1.3, dims=(32, 32, 32), centre=(15.5, 15.2, 15.5), radius=7.0, level=1),
+    "rigid": dict(rw=1.3, rigid=1),
+    "volume": dict(rw=1.3, kv=1.0),
+}
+
+
+def _job(rw, dims=(24, 24, 24), centre=(11.6, 11.4, 11.7), radius=3.5, level=2, rigid=0, kv=0.0):
+    spec = I.LatticeSpec(*dims, 0.8, **I.shear_walls(0.01))
+    xyz, tri = I.spheroid_mesh(level, (radius, radius, 0.8 * radius), centre)
+    body = I.BodySpec(rigid=rigid, ks0=0.0 if rigid else 0.01, kb=0.0 if rigid else 0.001, kv=kv, mass_ratio=2.0, mls_rw=rw)
+    return I.Job("mls", spec, body, xyz, tri, 20)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("name", list(CASES))
+def test_step_matches_oracle(api, orc, name):
+    """20 steps in a disturbed shear flow.  FP32 populations round at 6e-8 of order-one values, of
+    which u* ~ 1e-2 keeps about 1e-6 relative; the displacement and the vertex velocity inherit it,
+    the forces (differences of probe pressures) an order more."""
+    orc.set_threads(max(1, min(16, os.cpu_count() or 1)))
+    job = _job(**CASES[name])
+    nx, ny, nz = job.lattice.nx, job.lattice.ny, job.lattice.nz
+    rho, u = I.random_fields((nx, ny, nz), seed=4, amp_rho=1e-4, amp_u=5e-3)
+    u[0] += np.tile(np.repeat(0.02 * (np.arange(ny) / (ny - 1) - 0.5), nx), nz)
+    got, ref = api.Lattice(job.lattice), orc.Lattice(job.lattice)
+    out = []
+    for lat in (got, ref):
+        lat.init(rho, u)
+        b = lat.add_body(job.body, job.xyz, job.tri)
+        lat.step(job.steps)
+        x, v = lat.body_state(b)
+        f = lat.body_forces(b)[0]
+        out.append((lat.macros()[1], x - job.xyz, v, f))
+    for got_, ref_, tol in zip(*out, (2e-6, 5e-6, 5e-6, 5e-5)):
+        assert np.linalg.norm(got_ - ref_) <= tol * np.linalg.norm(ref_)
+
+
+@pytest.mark.gpu
+def test_both_forms_in_one_batch_equal_the_jobs_alone(api):
+    jobs = [_job(rw=1.3), _job(rw=1.45), _job(rw=1.3, rigid=1), _job(rw=1.45, rigid=1), _job(rw=1.3, kv=1.0)]
+    mix = api.Batch(jobs)
+    mix.step(20)
+    for j, job in enumerate(jobs):
+        alone = api.Batch([job])
+        alone.step(20)
+        for a, b in zip((mix.lattice(j),), (alone.lattice(0),)):
+            np.testing.assert_array_equal(a.macros()[1], b.macros()[1])
+            for p, q in zip((*a.body_state(0), *a.body_forces(0)), (*b.body_state(0), *b.body_forces(0))):
+                np.testing.assert_array_equal(p, q)
