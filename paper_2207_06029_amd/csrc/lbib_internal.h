@@ -80,9 +80,17 @@ constexpr bool table_ok() {
 static_assert(table_ok(), "D3Q19 tables inconsistent");
 
 // ---------------------------------------------------------------- tables
+// Elements from one population plane to the next in library-owned memory: planes start on 128 B
+// lines (both element sizes), so the sweep's stores fill whole lines also where the node count is odd.
+// Lines shared by two tiles are written in parts, by two XCDs: 193^3 FP32 sweeps in 202 us with
+// aligned planes, 264 us without (97^3 26.0 against 27.8, 135x131x141 73 against 85).
+constexpr long long PLANE_ALIGN = 64;
+constexpr long long plane_stride(long long n) { return (n + PLANE_ALIGN - 1) / PLANE_ALIGN * PLANE_ALIGN; }
+
 struct JobDev {
     int nx, ny, nz, storage;
     long long n;          // nodes
+    long long np;         // elements from one population plane to the next
     long long pop_off;    // element offset of this job's populations in the pool
     int tile0, ntiles;    // sweep tiles of this job
     float omega;          // 1 / tau

@@ -309,7 +309,7 @@ __device__ __forceinline__ void zou_he_corner(const JobDev& J, int s0, int s1, i
 template <typename S, bool ZH_CLOSURE = true, bool OFF32 = false, bool RAW = false, bool YZ_FAST = false>
 __device__ __forceinline__ void pull(const S* __restrict__ src, const JobDev& J, int x, int y,
                                      int z, long long k, float g[Q], unsigned walls) {
-    const long long N = J.n;
+    const long long N = J.np;
     const int nx = J.nx, ny = J.ny, nz = J.nz;
     const int sy = nx, sz = nx * ny;
     // linear displacement of the source for e = +1 (node c - 1) and e = -1 (node c + 1): a
@@ -578,7 +578,7 @@ __device__ __forceinline__ void sweep_node(const Pools& P, const JobDev& J, cons
                                            int x, int y, int z, int job, unsigned seed, unsigned walls) {
     float g[Q];
     pull<S, true, OFF32, true, YZ_FAST>(src, J, x, y, z, k, g, walls);
-    const long long N = J.n;
+    const long long N = J.np;
     const unsigned kb = (unsigned)k * (unsigned)sizeof(S);
     const long long pb = N * (long long)sizeof(S);   // bytes per population plane
     char* plane = (char*)dst;                         // plane i of the destination, stepped by pb
@@ -780,7 +780,7 @@ __global__ void __launch_bounds__(256) k_window_moments(Pools P, int from_b) {
     void* pop = from_b ? P.popB : P.popA;
     float4* mwin = P.mwin;
     long long* fwin = P.fwin;
-    loaded(J.nx, J.ny, J.nz, J.n, J.pop_off, J.walls, J.bc[0], J.bc[2], J.bc[4], J.wall_u[0][0], J.wall_u[2][0],
+    loaded(J.nx, J.ny, J.nz, J.np, J.pop_off, J.walls, J.bc[0], J.bc[2], J.bc[4], J.wall_u[0][0], J.wall_u[2][0],
            J.wall_u[5][2], d.o[0], d.w[0], d.w[1], d.w[2], nblk, lb, cap[0], off, pop, mwin, fwin);
     const unsigned stride = (unsigned)nblk * blockDim.x;
     const long long capn = (long long)cap[0] * cap[1] * cap[2];
@@ -932,14 +932,14 @@ __device__ __forceinline__ void set_one(const JobDev& J, S* __restrict__ dst, in
         }
     }
     if (nout == 0) {
-        Codec<S>::st(dst + (long long)i * J.n + s[0] + (long long)n[0] * (s[1] + (long long)n[1] * s[2]), gi);
+        Codec<S>::st(dst + (long long)i * J.np + s[0] + (long long)n[0] * (s[1] + (long long)n[1] * s[2]), gi);
     } else if (!zh && J.bc[face] == 2) {
         const float eu = cx(i) * uw[0] + cy(i) * uw[1] + cz(i) * uw[2];
-        Codec<S>::st(dst + (long long)opp(i) * J.n + k, gi - (float)(6.0 * wq(i)) * eu);
+        Codec<S>::st(dst + (long long)opp(i) * J.np + k, gi - (float)(6.0 * wq(i)) * eu);
     } else if (zh) {
         // the redirected slot: the edge and corner closure reads it as the mass the node sent
         // out through its walls, so the given density is kept
-        Codec<S>::st(dst + (long long)opp(i) * J.n + k, gi);
+        Codec<S>::st(dst + (long long)opp(i) * J.np + k, gi);
     }
 }
 

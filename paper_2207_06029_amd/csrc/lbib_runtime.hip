@@ -390,7 +390,7 @@ void Batch::job_from_desc(const lbib_lattice_desc& d, JobDev& J) {
     std::memset(&J, 0, sizeof J);
     J.nx = d.nx; J.ny = d.ny; J.nz = d.nz;
     J.storage = d.storage;
-    J.n = (long long)d.nx * d.ny * d.nz;
+    J.n = J.np = (long long)d.nx * d.ny * d.nz;
     J.omega = (float)(1.0 / d.tau);
     J.guo = (float)(1.0 - 1.0 / (2.0 * d.tau));
     J.nu = (float)((d.tau - 0.5) / 3.0);
@@ -421,8 +421,10 @@ lbib_status Batch::create_lattices(const std::vector<lbib_lattice_desc>& descs, 
     long long off = 0;
     for (size_t j = 0; j < descs.size(); ++j) {
         job_from_desc(descs[j], jobs[j]);
+        // a caller's workspace holds exactly 19 n values per buffer
+        if (!ws) jobs[j].np = plane_stride(jobs[j].n);
         jobs[j].pop_off = off;
-        off += 19LL * jobs[j].n;
+        off += 19LL * jobs[j].np;
         jobs[j].body0 = 0;
         jobs[j].nbodies = 0;
     }
@@ -430,7 +432,7 @@ lbib_status Batch::create_lattices(const std::vector<lbib_lattice_desc>& descs, 
     P.one_lattice = descs.size() == 1 ? 1 : 0;
     P.pop32 = 1;
     for (auto& J : jobs)
-        if (19LL * J.n * storage_bytes(storage) >= (1LL << 32)) P.pop32 = 0;
+        if (19LL * J.np * storage_bytes(storage) >= (1LL << 32)) P.pop32 = 0;
     lbib_status st = arena.alloc(pop_elems * storage_bytes(storage), &P.popA);
     if (st) return st;
     if ((st = arena.alloc(pop_elems * storage_bytes(storage), &P.popB))) return st;
@@ -1223,6 +1225,7 @@ lbib_status Batch::slot_admit(int s, const lbib_lattice_desc& d, const HostBody*
     if (n > caps.nodes) return fail(LBIB_ENOMEM, "lattice exceeds the slot capacity");
     JobDev J;
     job_from_desc(d, J);
+    if (plane_stride(n) <= caps.nodes) J.np = plane_stride(n);
     J.pop_off = (long long)s * 19 * caps.nodes;
     J.body0 = s;
     J.nbodies = 0;
