@@ -1,12 +1,12 @@
 // Immersed-boundary and structure kernels (Secs. 1.2-1.3).
 //
 // One MLS point (triangle centroid, probe or vertex) is evaluated by a group of 8 lanes (half a
-// DPP row); lane k owns nodes k, k + 8, k + 16 and k + 24 of the 3x3x3 block around the nearest
-// node.  Every node within r_w of the point lies in that block, so the group covers the whole
-// support of Eq. (intKernel).  The 4x4 moment matrix is accumulated and factorised in FP64 (every
-// lane of the group solves redundantly), so no lane waits on another except for the butterfly
-// sums.  The marker kernels run one-wave blocks of eight points: few lanes per point keep the
-// instructions per point low, which bounds the batched launches.
+// DPP row), which share the 3x3x3 nodes around the node nearest to the point.  The 4x4 moment matrix
+// is accumulated and factorised in FP64 (every lane of the group solves redundantly), so no lane
+// waits on another except for the butterfly sums.  The marker kernels run one-wave blocks of eight
+// points: few lanes per point keep the instructions per point low, which bounds the batched launches,
+// and a lone body's launches are chains of instructions and dependent reads, so they too follow the
+// instruction count (below: nodes outside the support dropped first, one window test per wave).
 //
 // Step order inside the time step n -> n+1:
 //   k_centroids  triangle blocks: force window of this step from the vertex bounding box,
@@ -29,8 +29,9 @@ namespace lbib {
 
 template <int CTRL>
 __device__ __forceinline__ double dpp_f64(double v) {
-    const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, 0xF, 0xF, false);
-    const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, 0xF, 0xF, false);
+    // every control used here reads a valid lane, so no value for the others is set up
+    const int lo = __builtin_amdgcn_mov_dpp(__double2loint(v), CTRL, 0xF, 0xF, true);
+    const int hi = __builtin_amdgcn_mov_dpp(__double2hiint(v), CTRL, 0xF, 0xF, true);
     return __hiloint2double(hi, lo);
 }
 // Sum over a group of G = 8 (half a DPP row) or 16 lanes (a row).  Lane exchanges xor 1 and xor 2
@@ -48,11 +49,23 @@ __device__ __forceinline__ double gsum(double v) {
     return v;
 }
 
+// The same for K values, level by level: a DPP move reads its operand two cycles after it was
+// written at the earliest, and the other values' additions fill that time.
+template <int K>
+__device__ __forceinline__ void gsum8(double v[K]) {
+#pragma unroll
+    for (int i = 0; i < K; ++i) v[i] += dpp_f64<0xB1>(v[i]);
+#pragma unroll
+    for (int i = 0; i < K; ++i) v[i] += dpp_f64<0x4E>(v[i]);
+#pragma unroll
+    for (int i = 0; i < K; ++i) v[i] += dpp_f64<0x141>(v[i]);
+}
+
 // Minimum / maximum over the wave: DPP within rows (quad permutes, half-mirror, mirror), then
 // two lane exchanges across rows.  Every lane ends with the result.
 template <int CTRL>
 __device__ __forceinline__ int dpp_i32(int v) {
-    return __builtin_amdgcn_update_dpp(0, v, CTRL, 0xF, 0xF, false);
+    return __builtin_amdgcn_mov_dpp(v, CTRL, 0xF, 0xF, true);
 }
 template <bool MAX>
 __device__ __forceinline__ int wave_minmax(int v) {
@@ -67,80 +80,70 @@ __device__ __forceinline__ int wave_minmax(int v) {
 }
 
 
-// Candidate nodes of an MLS point.  With c the node nearest to the point x on each axis, every node
-// within r_w < 1.5 of x lies in the 3x3x3 block around c, but never more than 15 of the 27 can.  Per
-// axis, call c near, the neighbour on x's side second and the other one far, at distances f, 1 - f
-// and 1 + f (f <= 1/2).  For r_w^2 < 2:
-//   - two far axes never: (1 + f)^2 + (1 + f')^2 >= 2;
-//   - far on a and second on b excludes far on b and second on a (the third axis alike), since
-//     (1 + f)^2 + (1 - f')^2 + (1 + f')^2 + (1 - f)^2 >= 4 > 2 r_w^2: only the one whose far axis
-//     has the smaller f can be a support node, and the two f then differ by (2 - r_w^2) / 2 at least.
-// That leaves the 8 corners of the cell around x (near or second on each axis) and, per non-empty
-// set of axes, the node that is far on the axis of the set with the smallest f, second on its other
-// axes and near off it: 8 + 7.  Corner i has second on the axes of the bits of i, far node i
-// belongs to the set FAR_SETS[i]; a point has 16 slots, and pair i holds corner i and far node i.
-// r_w^2 >= MLS_COMPACT_RW2 (the selection runs in FP32, so the bound leaves a margin) takes WIDE:
-// all 27 nodes.
-constexpr unsigned FAR_SETS = 0x07563421u;   // nibble i: axes x, y, z, xy, yz, xz, xyz, none
-
-// One MLS point, per lane of its G-lane group.  Compact: 8 pairs of slots (corner, far node), lane
-// l of 8 holds pair l (lanes 4..7 in reverse order, see gsum), lane l of 4 the pairs l and l + 4.
-// WIDE: lane l holds nodes l + G s of the block.
-template <int G, bool WIDE>
+// Nodes of an MLS point.  Every node within r_w < 1.5 of x lies in the 3x3x3 block around the node c
+// nearest to x; lane l of the point's 8 owns nodes l, l + 8, l + 16 and l + 24 of the block, its
+// class.  About 9 of the 27 are within r_w, so the lane drops the others before it does any work on
+// them: a class never holds more than three within r_w < sqrt(2), and rarely more than two.  Per axis
+// call c near, the neighbour on x's side second and the other one far, at distances f, 1 - f and
+// 1 + f (f <= 1/2).  Of two nodes that are second and far on one axis and far and second on another
+// only one can be within r_w, since their squared distances add up to 4 or more, and none is far on
+// two axes; that leaves at most two nodes of the classes 0, 1, 2 and 5, and the other classes have
+// three nodes.  Slots are filled in the class's order, so the sums over them are those over the whole
+// class bit for bit (the dropped nodes have weight zero).  The third slot is skipped in waves that
+// do not need it.  WIDE (r_w^2 >= MLS_COMPACT_RW2, with a margin for the FP32 test) keeps all four.
+template <bool WIDE>
 struct MlsLane {
-    static constexpr int N = WIDE ? (27 + G - 1) / G : 16 / G;   // slots per lane
+    static constexpr int N = WIDE ? 4 : 3;   // slots per lane
     int c[3];                    // node nearest to the point (unwrapped)
     int o[N][3];                 // slot's node relative to c
     bool active[N];              // within r_w of the point
-    double d[N][3];              // x_k - x
-    double W[N], phi[N];
+    double d0[N], d1[N], d2[N], r2[N];
+    double phi[N];
+    double gr[N][3];
+    bool more;                   // some lane of the wave uses the slots from the third on
 };
+#define MLS_SLOTS(s, m)                                                     \
+    _Pragma("unroll") for (int s = 0; s < MlsLane<WIDE>::N; ++s)            \
+        if (s < 2 || (m).more)
 
-template <int G, bool WIDE>
-__device__ __forceinline__ void mls_locate(const double xp[3], double rw2, int lane, MlsLane<G, WIDE>& m) {
+template <bool WIDE>
+__device__ __forceinline__ void mls_locate(const double xp[3], double rw2, int lane, MlsLane<WIDE>& m) {
+    // the point's coordinates are taken as rounded, not fused with the product that formed them
+#pragma clang fp contract(off)
     double dn[3];
-    int sg[3];       // direction of the second node
     float f[3];
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
         const double n = floor(xp[a] + 0.5);
         m.c[a] = (int)n;
-        dn[a] = n - xp[a];   // exact, and so is the offset added below
-        sg[a] = dn[a] > 0.0 ? -1 : 1;
-        f[a] = fabsf((float)dn[a]);
+        dn[a] = n - xp[a];   // exact, and so is the offset added to it below
+        f[a] = (float)dn[a];
     }
+    // the class's nodes within r_w, by their FP32 distance with a margin; FP64 decides below
+    unsigned set = WIDE ? 15u : 0u;
+    if (!WIDE) {
+        const float r2max = (float)rw2 + 1e-4f;
 #pragma unroll
-    for (int s = 0; s < MlsLane<G, WIDE>::N; ++s) {
-        bool some = true;
-        if (WIDE) {
-            const int k = lane + G * s;
-            some = k < 27;
-            m.o[s][0] = k % 3 - 1;
-            m.o[s][1] = (k / 3) % 3 - 1;
-            m.o[s][2] = some ? k / 9 - 1 : 0;
-        } else {
-            const int i = G == 8 ? (lane < 4 ? lane : 11 - lane) : lane + 4 * (s / 2);
-            if (s % 2 == 0) {
-#pragma unroll
-                for (int a = 0; a < 3; ++a) m.o[s][a] = (i >> a) & 1 ? sg[a] : 0;
-            } else {
-                const unsigned set = (FAR_SETS >> (4 * i)) & 7u;
-                const float f0 = set & 1u ? f[0] : 4.f, f1 = set & 2u ? f[1] : 4.f, f2 = set & 4u ? f[2] : 4.f;
-                const bool far0 = f0 <= f1 && f0 <= f2, far1 = !far0 && f1 <= f2;
-                some = set != 0u;
-                m.o[s][0] = set & 1u ? (far0 ? -sg[0] : sg[0]) : 0;
-                m.o[s][1] = set & 2u ? (far1 ? -sg[1] : sg[1]) : 0;
-                m.o[s][2] = set & 4u ? (far0 || far1 ? sg[2] : -sg[2]) : 0;
-            }
+        for (int s = 0; s < 4; ++s) {
+            const int k = lane + 8 * s, q3 = (k * 171) >> 9, q9 = (k * 57) >> 9;
+            const float x = f[0] + (float)(k - 3 * q3 - 1), y = f[1] + (float)(q3 - 3 * q9 - 1), z = f[2] + (float)(q9 - 1);
+            set |= (fmaf(z, z, fmaf(y, y, x * x)) <= r2max && k < 27 ? 1u : 0u) << s;
         }
-        double r2 = 0.0;
-#pragma unroll
-        for (int a = 0; a < 3; ++a) {
-            m.d[s][a] = dn[a] + (double)m.o[s][a];
-            r2 = a == 0 ? m.d[s][a] * m.d[s][a] : fma(m.d[s][a], m.d[s][a], r2);
-        }
-        m.active[s] = some && r2 <= rw2;
-        m.W[s] = r2;
+    }
+    m.more = WIDE || __any((set & (set - 1u) & ((set & (set - 1u)) - 1u)) != 0u);
+    MLS_SLOTS(s, m) {
+        const int pick = WIDE ? s : __ffs(set) - 1;   // -1: none left
+        const bool some = WIDE ? lane + 8 * s < 27 : set != 0u;
+        set &= set - 1u;
+        const int k = some ? lane + 8 * pick : 13, q3 = (k * 171) >> 9, q9 = (k * 57) >> 9;
+        m.o[s][0] = k - 3 * q3 - 1;
+        m.o[s][1] = q3 - 3 * q9 - 1;
+        m.o[s][2] = q9 - 1;
+        m.d0[s] = dn[0] + (double)m.o[s][0];
+        m.d1[s] = dn[1] + (double)m.o[s][1];
+        m.d2[s] = dn[2] + (double)m.o[s][2];
+        m.r2[s] = fma(m.d2[s], m.d2[s], fma(m.d0[s], m.d0[s], m.d1[s] * m.d1[s]));
+        m.active[s] = some && m.r2[s] <= rw2;
     }
 }
 
@@ -152,99 +155,65 @@ __device__ __forceinline__ double rcp64(double x) {
     return r;
 }
 
-// Sum over the point's lanes of a per-lane value given as the lane's sums over its pairs of slots.
-// Four lanes hold two pairs each (p0, p1), eight lanes one: the tree adds pair i and pair i + 4
-// first in both, so the two forms give the same bits (and a job the same results in both).
-template <int G, bool WIDE>
-__device__ __forceinline__ double psum(double p0, double p1) {
-    if (G == 4) {
-        double v = p0 + p1;
-        v += dpp_f64<0xB1>(v);
-        v += dpp_f64<0x4E>(v);
-        return v;
+// Shape functions phi_k = [A^{-1} W_k p_k]_0 and (optionally) their gradients, A = sum W p p^T,
+// p = (1, d), W = exp(-(|d| / (r_w alpha))^2) (Eqs. l2norm, intKernel).  The weights are
+// evaluated in FP32; the moment matrix is accumulated and factorised (A = L D L^T, unit L) in
+// FP64 on every lane.
+template <bool WIDE, bool FUSE = true>
+__device__ __forceinline__ void mls_solve(MlsLane<WIDE>& m, float wq, bool want_grad, int& err) {
+    double W[MlsLane<WIDE>::N];
+    double A[10] = {};   // 00 01 02 03 11 12 13 22 23 33
+    MLS_SLOTS(s, m) {
+        W[s] = m.active[s] ? (double)expf(-wq * (float)m.r2[s]) : 0.0;
+        const double w = W[s], d0 = m.d0[s], d1 = m.d1[s], d2 = m.d2[s];
+        A[0] += w; A[1] += w * d0; A[2] += w * d1; A[3] += w * d2;
+        A[4] += w * d0 * d0; A[5] += w * d0 * d1; A[6] += w * d0 * d2;
+        A[7] += w * d1 * d1; A[8] += w * d1 * d2; A[9] += w * d2 * d2;
     }
-    p0 += dpp_f64<0x141>(p0);   // row_half_mirror: lane 7 - l holds pair l + 4
-    p0 += dpp_f64<0xB1>(p0);
-    p0 += dpp_f64<0x4E>(p0);
-    return p0;
-}
-
-// sum_k c_k q_k over the point for per-slot coefficients and values
-template <int G, bool WIDE>
-__device__ __forceinline__ double pdot(const double* c, const double* q) {
-#pragma clang fp contract(off)
-    constexpr int N = MlsLane<G, WIDE>::N, PAIRS = !WIDE && G == 4 ? 2 : 1;
-    double t[PAIRS];
-#pragma unroll
-    for (int s = 0; s < N; ++s) {
-        double& a = t[PAIRS == 2 ? s / 2 : 0];
-        a = s == 0 || (PAIRS == 2 && s == 2) ? c[s] * q[s] : fma(c[s], q[s], a);
-    }
-    return psum<G, WIDE>(t[0], t[PAIRS - 1]);
-}
-
-// Moment matrix A = sum W p p^T, p = (1, d), W = exp(-(|d| / (r_w alpha))^2) (Eqs. l2norm,
-// intKernel), factorised as L D L^T (unit L) in FP64 on every lane; the weights are evaluated in
-// FP32.  phi_k = [A^{-1} W_k p_k]_0; with GRAD, gn_k = n . [A^{-1} W_k p_k]_{1..3} and the rows
-// themselves in gr (the diffuse derivatives along n and along the axes).
-// Products and sums are written as explicit multiplications and fused multiply-adds with
-// contraction off, so that the four- and eight-lane forms round alike.
-template <int G, bool WIDE, bool GRAD>
-__device__ __forceinline__ void mls_solve(MlsLane<G, WIDE>& m, float wq, int& err, const double* nrm = nullptr,
-                                          double (*gr)[3] = nullptr, double* gn = nullptr) {
-#pragma clang fp contract(off)
-    constexpr int N = MlsLane<G, WIDE>::N;
-    constexpr int PAIRS = !WIDE && G == 4 ? 2 : 1;   // sums kept apart per pair (see psum)
-    double t[PAIRS][10];
-#pragma unroll
-    for (int s = 0; s < N; ++s) {
-        const double w = m.active[s] ? (double)expf(-wq * (float)m.W[s]) : 0.0;
-        m.W[s] = w;
-        const double d0 = m.d[s][0], d1 = m.d[s][1], d2 = m.d[s][2];
-        const double w0 = w * d0, w1 = w * d1, w2 = w * d2;
-        double* q = t[PAIRS == 2 ? s / 2 : 0];
-        if (s == 0 || (PAIRS == 2 && s == 2)) {
-            q[0] = w; q[1] = w0; q[2] = w1; q[3] = w2;
-            q[4] = w0 * d0; q[5] = w0 * d1; q[6] = w0 * d2;
-            q[7] = w1 * d1; q[8] = w1 * d2; q[9] = w2 * d2;
-        } else {
-            q[0] += w; q[1] += w0; q[2] += w1; q[3] += w2;
-            q[4] = fma(w0, d0, q[4]); q[5] = fma(w0, d1, q[5]); q[6] = fma(w0, d2, q[6]);
-            q[7] = fma(w1, d1, q[7]); q[8] = fma(w1, d2, q[8]); q[9] = fma(w2, d2, q[9]);
-        }
-    }
-    double A[10];
-#pragma unroll
-    for (int k = 0; k < 10; ++k) A[k] = psum<G, WIDE>(t[0][k], t[PAIRS - 1][k]);
-    const double a01 = A[1], a02 = A[2], a03 = A[3];
+    gsum8<10>(A);
+    const double a00 = A[0], a01 = A[1], a02 = A[2], a03 = A[3], a11 = A[4], a12 = A[5], a13 = A[6], a22 = A[7],
+                 a23 = A[8], a33 = A[9];
     // A = L D L^T
-    const double e0 = A[0], i0 = rcp64(e0);
+    const double e0 = a00;
+    const double i0 = rcp64(e0);
     const double l10 = a01 * i0, l20 = a02 * i0, l30 = a03 * i0;
-    const double e1 = fma(-l10, a01, A[4]), i1 = rcp64(e1);
-    const double b21 = fma(-l20, a01, A[5]), b31 = fma(-l30, a01, A[6]);   // D-scaled column entries
+    const double e1 = a11 - l10 * a01;
+    const double i1 = rcp64(e1);
+    const double b21 = a12 - l20 * a01, b31 = a13 - l30 * a01;   // D-scaled column entries
     const double l21 = b21 * i1, l31 = b31 * i1;
-    const double e2 = fma(-l21, b21, fma(-l20, a02, A[7])), i2 = rcp64(e2);
-    const double b32 = fma(-l31, b21, fma(-l30, a02, A[8]));
+    const double e2 = a22 - l20 * a02 - l21 * b21;
+    const double i2 = rcp64(e2);
+    const double b32 = a23 - l30 * a02 - l31 * b21;
     const double l32 = b32 * i2;
-    const double e3 = fma(-l32, b32, fma(-l31, b31, fma(-l30, a03, A[9]))), i3 = rcp64(e3);
+    const double e3 = a33 - l30 * a03 - l31 * b31 - l32 * b32;
+    const double i3 = rcp64(e3);
     if (!(e0 > 0.0 && e1 > 0.0 && e2 > 0.0 && e3 > 0.0)) err |= FLAG_NONFINITE;
-#pragma unroll
-    for (int s = 0; s < N; ++s) {
-        // v = A^{-1} p_k: L y = p, z = D^{-1} y, L^T v = z
-        const double y1 = m.d[s][0] - l10;
-        const double y2 = fma(-l21, y1, m.d[s][1] - l20);
-        const double y3 = fma(-l32, y2, fma(-l31, y1, m.d[s][2] - l30));
+    MLS_SLOTS(s, m) {
+        // v = A^{-1} p_k: L y = p, z = D^{-1} y, L^T v = z.  FUSE: the first column of L, a0j / e0,
+        // enters the differences as the unrounded product
+        const double y1 = FUSE ? fma(-i0, a01, m.d0[s]) : m.d0[s] - l10;
+        const double y2 = fma(-l21, y1, FUSE ? fma(-i0, a02, m.d1[s]) : m.d1[s] - l20);
+        const double y3 = fma(-l32, y2, fma(-l31, y1, FUSE ? fma(-i0, a03, m.d2[s]) : m.d2[s] - l30));
         const double v3 = y3 * i3;
-        const double v2 = fma(-l32, v3, y2 * i2);
-        const double v1 = fma(-l31, v3, fma(-l21, v2, y1 * i1));
+        const double v2 = fma(y2, i2, -(l32 * v3));
+        const double v1 = fma(-l31, v3, fma(y1, i1, -(l21 * v2)));
         const double v0 = fma(-l30, v3, fma(-l20, v2, fma(-l10, v1, i0)));
-        const double w = m.W[s];
-        m.phi[s] = w * v0;
-        if (GRAD) {
-            gr[s][0] = w * v1; gr[s][1] = w * v2; gr[s][2] = w * v3;
-            gn[s] = fma(gr[s][2], nrm[2], fma(gr[s][1], nrm[1], gr[s][0] * nrm[0]));
-        }
+        m.phi[s] = W[s] * v0;
+        if (want_grad) { m.gr[s][0] = W[s] * v1; m.gr[s][1] = W[s] * v2; m.gr[s][2] = W[s] * v3; }
     }
+}
+
+// The lane's part of sum_k c_k q_k over the point for per-node coefficients c (phi or a gradient row)
+// and field values q (component `comp` of the moments: 0 rho - 1, 1..3 u*)
+template <bool WIDE>
+__device__ __forceinline__ double point_dot(const MlsLane<WIDE>& m, const double* c, int cstride,
+                                            const float4 mom[MlsLane<WIDE>::N], int comp) {
+    double acc = 0.0;
+    MLS_SLOTS(s, m) {
+        const float q = comp == 0 ? mom[s].x : (comp == 1 ? mom[s].y : (comp == 2 ? mom[s].z : mom[s].w));
+        acc += c[s * cstride] * (double)q;
+    }
+    return acc;
 }
 
 // Index of every slot's node in a window of layout d (see WinDesc).  Points whose 3x3x3 block lies
@@ -252,10 +221,9 @@ __device__ __forceinline__ void mls_solve(MlsLane<G, WIDE>& m, float wq, int& er
 // per wave): no wrap, no test per node, and the inactive slots hold valid indices too, so the
 // caller loads all of them without a branch.  The second form wraps periodic axes, reports support
 // nodes beyond a wall or the window, and gives their slots index 0.
-template <int G, bool WIDE>
-__device__ __forceinline__ void mls_index(const JobDev& J, const WinDesc& d, MlsLane<G, WIDE>& m,
-                                          unsigned idx[MlsLane<G, WIDE>::N], int& err) {
-    constexpr int N = MlsLane<G, WIDE>::N;
+template <bool WIDE>
+__device__ __forceinline__ void mls_index(const JobDev& J, const WinDesc& d, MlsLane<WIDE>& m,
+                                          unsigned idx[MlsLane<WIDE>::N], int& err) {
     const int n[3] = {J.nx, J.ny, J.nz};
     const int s1 = d.w[0], s2 = d.w[0] * d.w[1];
     bool in = s2 < (1 << 23);   // 24-bit products below
@@ -269,13 +237,11 @@ __device__ __forceinline__ void mls_index(const JobDev& J, const WinDesc& d, Mls
     }
     if (__all(in)) {
         const int base = (m.c[0] - d.b[0]) + s1 * (m.c[1] - d.b[1]) + s2 * (m.c[2] - d.b[2]);
-#pragma unroll
-        for (int s = 0; s < N; ++s)
+        MLS_SLOTS(s, m)
             idx[s] = (unsigned)(base + m.o[s][0] + __mul24(m.o[s][1], s1) + __mul24(m.o[s][2], s2));
         return;
     }
-#pragma unroll
-    for (int s = 0; s < N; ++s) {
+    MLS_SLOTS(s, m) {
         unsigned i = 0, st = 1;
         bool ok = true;
 #pragma unroll
@@ -452,10 +418,10 @@ __device__ void hinge_forces(const Pools& P, const BodyDev& B, int e, double out
 // Round to nearest even into int64, as __double2ll_rn, without its software sequence: for
 // |v| < 2^51, v + 1.5 * 2^52 lies in [2^52, 2^53), where the addition itself rounds v to an
 // integer in the low mantissa bits.  The addition must not be fused with the product that
-// formed v.
-__device__ __forceinline__ long long fix_rn(double v) {
+// formed v.  Larger values (small false) are left to the caller, one vote for all of a wave's.
+__device__ __forceinline__ long long fix_rn(double v, bool& small) {
 #pragma clang fp contract(off)
-    if (!(fabs(v) < 2251799813685248.0)) return __double2ll_rn(v);
+    small = small && fabs(v) < 2251799813685248.0;
     const double t = v + 6755399441055744.0;
     return __double_as_longlong(t) - 0x4338000000000000LL;
 }
@@ -477,12 +443,12 @@ __device__ __forceinline__ long long fix_rn(double v) {
 // Without fold, fd_in is the window the window kernel of the previous step published.
 constexpr int SPREAD_LDS_Z = 6;
 
-template <int G, bool WIDE>
+template <bool WIDE>
 __device__ __forceinline__ void spread_block(const Pools& P, const JobDev& J, const BodyDev& B, int b,
                                              int blk, bool fold, const int vb[6], const WinDesc& fd_in,
-                                             bool live, MlsLane<G, WIDE>& m,
-                                             const long long fx[MlsLane<G, WIDE>::N][3], int& err) {
-    constexpr int N = MlsLane<G, WIDE>::N;
+                                             bool live, MlsLane<WIDE>& m,
+                                             const long long fx[MlsLane<WIDE>::N][3], int& err) {
+    constexpr int N = MlsLane<WIDE>::N;
     static_assert(IB_BLOCK == 64, "the block is one wave: its boxes are wave reductions");
     __shared__ unsigned long long s_acc[3][64 * SPREAD_LDS_Z];
     const long long capn = (long long)B.win_cap[0] * B.win_cap[1] * B.win_cap[2];
@@ -506,9 +472,8 @@ __device__ __forceinline__ void spread_block(const Pools& P, const JobDev& J, co
     const bool use_lds = w[0] <= 8 && w[1] <= 8 && w[2] <= SPREAD_LDS_Z;   // uniform over the block
     unsigned idx[N];
     if (!use_lds) {
-        mls_index<G, WIDE>(J, fd, m, idx, err);
-#pragma unroll
-        for (int s = 0; s < N; ++s)
+        mls_index<WIDE>(J, fd, m, idx, err);
+        MLS_SLOTS(s, m)
             if (live && m.active[s])
                 for (int c = 0; c < 3; ++c)
                     if (fx[s][c]) atomicAdd(fw0 + c * capn + idx[s], (unsigned long long)fx[s][c]);
@@ -520,8 +485,7 @@ __device__ __forceinline__ void spread_block(const Pools& P, const JobDev& J, co
     __syncthreads();
     if (live) {
         const int base = (m.c[0] - o[0]) + 8 * (m.c[1] - o[1]) + 64 * (m.c[2] - o[2]);
-#pragma unroll
-        for (int s = 0; s < N; ++s) {
+        MLS_SLOTS(s, m) {
             const int li = base + m.o[s][0] + 8 * m.o[s][1] + 64 * m.o[s][2];
             if (m.active[s])
                 for (int c = 0; c < 3; ++c) atomicAdd(&s_acc[c][li], (unsigned long long)fx[s][c]);
@@ -561,9 +525,9 @@ __device__ __forceinline__ void spread_block(const Pools& P, const JobDev& J, co
 }
 
 // ---------------------------------------------------------------- centroids (+ hinges)
-template <bool SOLO, int G, bool WIDE>
+template <bool SOLO, bool WIDE>
 __global__ void __launch_bounds__(IB_BLOCK, SOLO ? 1 : 4) k_centroids(Pools P, int nblk_tri, int fold) {
-    constexpr int N = MlsLane<G, WIDE>::N, PTS = IB_BLOCK / G;
+    constexpr int N = MlsLane<WIDE>::N, PTS = IB_BLOCK / MLS_GROUP;
     if ((int)blockIdx.x >= nblk_tri) {
         // edge blocks: one thread per hinge of a membrane
         const int eb = blockIdx.x - nblk_tri;
@@ -582,7 +546,7 @@ __global__ void __launch_bounds__(IB_BLOCK, SOLO ? 1 : 4) k_centroids(Pools P, i
     if ((B.rw2 >= MLS_COMPACT_RW2) != WIDE) return;   // the other form's launch
     const JobDev J = body_job<SOLO>(P, B);   // copied before the first store: one round of scalar loads
     BodyState& S = P.bstate[b];
-    const int grp = threadIdx.x / G, lane = threadIdx.x % G;
+    const int grp = threadIdx.x / MLS_GROUP, lane = threadIdx.x % MLS_GROUP;
     const int blk = blockIdx.x - B.blk_c0;
     const bool live = blk * PTS + grp < B.nt;
     const int t = live ? blk * PTS + grp : B.nt - 1;   // a spare group repeats the last triangle
@@ -617,13 +581,14 @@ __global__ void __launch_bounds__(IB_BLOCK, SOLO ? 1 : 4) k_centroids(Pools P, i
         ab[a] = xb_[a] - xa[a];
         ac[a] = xc[a] - xa[a];
     }
-    MlsLane<G, WIDE> m;
-    mls_locate<G, WIDE>(cen, B.rw2, lane, m);
+    MlsLane<WIDE> m;
+    mls_locate<WIDE>(cen, B.rw2, lane, m);
     unsigned idx[N];
     float4 mom[N];
-    mls_index<G, WIDE>(J, md, m, idx, err);
-#pragma unroll
-    for (int s = 0; s < N; ++s) mom[s] = P.mwin[B.win_off + idx[s]];
+    mls_index<WIDE>(J, md, m, idx, err);
+    // a lone body's launch is a latency chain: its moment loads go out before the solve; a
+    // batched launch is throughput-bound and loads them after it, to hold fewer registers
+    if (SOLO) MLS_SLOTS(s, m) mom[s] = P.mwin[B.win_off + idx[s]];
     cross3(ab, ac, nn);
     const double A = 0.5 * sqrt(dot3(nn, nn));
     if (live && lane == 0) {
@@ -631,14 +596,20 @@ __global__ void __launch_bounds__(IB_BLOCK, SOLO ? 1 : 4) k_centroids(Pools P, i
         double* g = P.tgeo + 6 * (B.t0 + t);
         for (int a = 0; a < 3; ++a) { g[a] = cen[a]; g[3 + a] = nn[a]; }
     }
-    mls_solve<G, WIDE, false>(m, B.wq, err);
-    double U[3];
-    for (int a = 0; a < 3; ++a) {
-        double q[N];
-#pragma unroll
-        for (int s = 0; s < N; ++s) q[s] = a == 0 ? mom[s].y : (a == 1 ? mom[s].z : mom[s].w);
-        U[a] = pdot<G, WIDE>(m.phi, q);
+    double Vt = 0.0;
+    if (!B.rigid && B.kv != 0.0) {
+        // signed volume of the tetrahedron (r, a, b, c), r = vertex 0 of the body
+        double r0[3], pa[3], pb[3], pc[3], bc[3];
+        load3(P.x + 3 * B.v0, r0);
+        for (int a = 0; a < 3; ++a) { pa[a] = xa[a] - r0[a]; pb[a] = xb_[a] - r0[a]; pc[a] = xc[a] - r0[a]; }
+        cross3(pb, pc, bc);
+        Vt = dot3(pa, bc) * (1.0 / 6.0);
     }
+    mls_solve<WIDE, SOLO>(m, B.wq, false, err);
+    if (!SOLO) MLS_SLOTS(s, m) mom[s] = P.mwin[B.win_off + idx[s]];
+    double U[3];
+    for (int a = 0; a < 3; ++a) U[a] = point_dot<WIDE>(m, m.phi, 1, mom, 1 + a);
+    gsum8<3>(U);
     // desired boundary velocity U_b (Sec. 1.2): membranes average their vertex velocities,
     // rigid bodies move the marker with the body
     if (B.rigid) {
@@ -650,22 +621,19 @@ __global__ void __launch_bounds__(IB_BLOCK, SOLO ? 1 : 4) k_centroids(Pools P, i
     const double fs = A * B.shell_h * FIX_SCALE;
     long long fx[N][3];   // fixed-point force of each slot's node
     for (int a = 0; a < 3; ++a) U[a] = Ub[a] - U[a];
-#pragma unroll
-    for (int s = 0; s < N; ++s)
-        for (int a = 0; a < 3; ++a) fx[s][a] = fix_rn(fs * m.phi[s] * U[a]);
-    spread_block<G, WIDE>(P, J, B, b, blk, fold != 0, vb, fd_pub, live, m, fx, err);
+    bool small = true;
+    MLS_SLOTS(s, m)
+        for (int a = 0; a < 3; ++a) fx[s][a] = fix_rn(fs * m.phi[s] * U[a], small);
+    if (!__all(small)) {
+        MLS_SLOTS(s, m)
+            for (int a = 0; a < 3; ++a) fx[s][a] = __double2ll_rn(fs * m.phi[s] * U[a]);
+    }
+    spread_block<WIDE>(P, J, B, b, blk, fold != 0, vb, fd_pub, live, m, fx, err);
     if (err && live) atomicOr(P.flags + B.job, err);
     if (B.rigid || B.kv == 0.0) return;
-    // signed volume of the tetrahedron (r, a, b, c), r = vertex 0 of the body; one partial per
-    // VOL_GROUP triangles, folded into V by k_fold_bodies
+    // one partial of the volume per VOL_GROUP triangles, folded into V by k_fold_bodies
     __shared__ double vol[PTS];
-    if (lane == 0) {
-        double r0[3], pa[3], pb[3], pc[3], bc[3];
-        load3(P.x + 3 * B.v0, r0);
-        for (int a = 0; a < 3; ++a) { pa[a] = xa[a] - r0[a]; pb[a] = xb_[a] - r0[a]; pc[a] = xc[a] - r0[a]; }
-        cross3(pb, pc, bc);
-        vol[grp] = live ? dot3(pa, bc) * (1.0 / 6.0) : 0.0;
-    }
+    if (lane == 0) vol[grp] = live ? Vt : 0.0;
     __syncthreads();
     constexpr int PARTS = PTS / VOL_GROUP;
     const int part = blk * PARTS + (int)threadIdx.x;
@@ -680,35 +648,30 @@ __global__ void __launch_bounds__(IB_BLOCK, SOLO ? 1 : 4) k_centroids(Pools P, i
 // Fluid velocity at every membrane vertex from the moments of f^{n+1} (the tentative velocity
 // of Eq. verletPos).  It needs nothing from the probes, so its blocks ride in the probe launch
 // and the vertex kernel only gathers forces and moves the vertices.  One group per vertex.
-template <bool SOLO, int G, bool WIDE>
+template <bool SOLO, bool WIDE>
 __device__ void vertex_velocity_block(const Pools& P, int vb) {
-    constexpr int N = MlsLane<G, WIDE>::N, PTS = IB_BLOCK / G;
+    constexpr int N = MlsLane<WIDE>::N, PTS = IB_BLOCK / MLS_GROUP;
     const int b = block_body<SOLO>(P, P.blk_body_u, vb);
     const BodyDev& B = body_of<SOLO>(P, b);
     if (B.rigid || (B.rw2 >= MLS_COMPACT_RW2) != WIDE) return;
     const JobDev J = body_job<SOLO>(P, B);
-    const int grp = threadIdx.x / G, lane = threadIdx.x % G;
+    const int grp = threadIdx.x / MLS_GROUP, lane = threadIdx.x % MLS_GROUP;
     const bool live = (vb - B.blk_u0) * PTS + grp < B.nv;
     const long long gv = B.v0 + (live ? (vb - B.blk_u0) * PTS + grp : B.nv - 1);
     int err = 0;
     double x[3];
     load3(P.x + 3 * gv, x);
     const WinDesc md = P.mdesc[b];
-    MlsLane<G, WIDE> m;
+    MlsLane<WIDE> m;
     unsigned idx[N];
     float4 mom[N];
-    mls_locate<G, WIDE>(x, B.rw2, lane, m);
-    mls_index<G, WIDE>(J, md, m, idx, err);
-#pragma unroll
-    for (int s = 0; s < N; ++s) mom[s] = P.mwin[B.win_off + idx[s]];
-    mls_solve<G, WIDE, false>(m, B.wq, err);
+    mls_locate<WIDE>(x, B.rw2, lane, m);
+    mls_index<WIDE>(J, md, m, idx, err);
+    MLS_SLOTS(s, m) mom[s] = P.mwin[B.win_off + idx[s]];
+    mls_solve<WIDE>(m, B.wq, false, err);
     double u[3];
-    for (int a = 0; a < 3; ++a) {
-        double q[N];
-#pragma unroll
-        for (int s = 0; s < N; ++s) q[s] = a == 0 ? mom[s].y : (a == 1 ? mom[s].z : mom[s].w);
-        u[a] = pdot<G, WIDE>(m.phi, q);
-    }
+    for (int a = 0; a < 3; ++a) u[a] = point_dot<WIDE>(m, m.phi, 1, mom, 1 + a);
+    gsum8<3>(u);
     if (live && lane < 3) P.u0v[3 * gv + lane] = lane == 0 ? u[0] : (lane == 1 ? u[1] : u[2]);
     if (err && live) atomicOr(P.flags + B.job, err);
 }
@@ -716,14 +679,11 @@ __device__ void vertex_velocity_block(const Pools& P, int vb) {
 // ---------------------------------------------------------------- triangles (probes)
 // Group 2k evaluates the outer probe of triangle k of the block, group 2k+1 the inner one.
 // Blocks from nblk_tri on compute the vertex velocities instead.
-// The stress enters only as tau . n: with v1..v3 the gradient rows of the shape functions,
-// [(grad u + grad u^T) n]_i = sum_k (n . v_k) u_i,k + v_i,k (u_k . n), so a probe needs four sums
-// over its nodes, rho - 1 and these three, not rho - 1 and the nine components of grad u.
-template <bool SOLO, int G, bool WIDE>
+template <bool SOLO, bool WIDE>
 __global__ void __launch_bounds__(IB_BLOCK, 4) k_triangles(Pools P, int nblk_tri) {
-    constexpr int N = MlsLane<G, WIDE>::N, PTS = IB_BLOCK / G, TRIS = PTS / 2;
+    constexpr int N = MlsLane<WIDE>::N, PTS = IB_BLOCK / MLS_GROUP, TRIS = PTS / 2;
     if ((int)blockIdx.x >= nblk_tri) {
-        vertex_velocity_block<SOLO, G, WIDE>(P, blockIdx.x - nblk_tri);
+        vertex_velocity_block<SOLO, WIDE>(P, blockIdx.x - nblk_tri);
         return;
     }
     const int b = block_body<SOLO>(P, P.blk_body_t, blockIdx.x);
@@ -731,7 +691,7 @@ __global__ void __launch_bounds__(IB_BLOCK, 4) k_triangles(Pools P, int nblk_tri
     if ((B.rw2 >= MLS_COMPACT_RW2) != WIDE) return;   // the other form's launch
     const JobDev J = body_job<SOLO>(P, B);   // copied before the first store: one round of scalar loads
     BodyState& S = P.bstate[b];
-    const int grp = threadIdx.x / G, lane = threadIdx.x % G;
+    const int grp = threadIdx.x / MLS_GROUP, lane = threadIdx.x % MLS_GROUP;
     const int blk = blockIdx.x - B.blk_t0;
     const int k = grp >> 1, side = grp & 1;
     const bool live = blk * TRIS + k < B.nt;
@@ -742,44 +702,43 @@ __global__ void __launch_bounds__(IB_BLOCK, 4) k_triangles(Pools P, int nblk_tri
     const double* g = P.tgeo + 6 * (B.t0 + t);
     double cen[3], nn[3], nrm[3], xp[3];
     for (int a = 0; a < 3; ++a) { cen[a] = g[a]; nn[a] = g[3 + a]; }
-    const double ln = sqrt(dot3(nn, nn));
+    const double ln = sqrt(dot3(nn, nn)), A = 0.5 * ln;
     const double sg = side == 0 ? B.probe : -B.probe;
     for (int a = 0; a < 3; ++a) {
         nrm[a] = nn[a] / ln;
         xp[a] = cen[a] + sg * nrm[a];
     }
-    MlsLane<G, WIDE> m;
+    MlsLane<WIDE> m;
     unsigned idx[N];
     float4 mom[N];
-    mls_locate<G, WIDE>(xp, B.rw2, lane, m);
-    mls_index<G, WIDE>(J, md, m, idx, err);
-#pragma unroll
-    for (int s = 0; s < N; ++s) mom[s] = P.mwin[B.win_off + idx[s]];
-    double gr[N][3], gn[N], one[N];
-    mls_solve<G, WIDE, true>(m, B.wq, err, nrm, gr, gn);
-    double q[N], un[N], T[3];
-#pragma unroll
-    for (int s = 0; s < N; ++s) {
-        q[s] = mom[s].x;
-        un[s] = fma((double)mom[s].w, nrm[2], fma((double)mom[s].z, nrm[1], (double)mom[s].y * nrm[0]));
-        one[s] = 1.0;
+    mls_locate<WIDE>(xp, B.rw2, lane, m);
+    mls_index<WIDE>(J, md, m, idx, err);
+    MLS_SLOTS(s, m) mom[s] = P.mwin[B.win_off + idx[s]];
+    mls_solve<WIDE>(m, B.wq, true, err);
+    // interpolated rho - 1 and the gradient rows of u* (diffuse derivatives), here and at the
+    // triangle's other probe, in the other half of the 16 lanes
+    double pp[10], pm[10];
+    pp[0] = point_dot<WIDE>(m, m.phi, 1, mom, 0);
+    for (int j = 0; j < 3; ++j) {
+        pp[1 + j] = point_dot<WIDE>(m, &m.gr[0][j], 3, mom, 1);
+        pp[4 + j] = point_dot<WIDE>(m, &m.gr[0][j], 3, mom, 2);
+        pp[7 + j] = point_dot<WIDE>(m, &m.gr[0][j], 3, mom, 3);
     }
-    const double r = pdot<G, WIDE>(m.phi, q);   // rho - 1 at the probe
-    for (int i = 0; i < 3; ++i) {
-#pragma unroll
-        for (int s = 0; s < N; ++s)
-            q[s] = fma(gr[s][i], un[s], gn[s] * (double)(i == 0 ? mom[s].y : (i == 1 ? mom[s].z : mom[s].w)));
-        T[i] = pdot<G, WIDE>(one, q);
-    }
+    gsum8<10>(pp);
+    for (int i = 0; i < 10; ++i) pm[i] = dpp_f64<0x128>(pp[i]);   // row_ror:8
     if (err && live) atomicOr(P.flags + B.job, err);
-    // outer minus inner probe: p = c_s^2 rho, tau = rho nu (grad u + grad u^T)
-    const double nu = J.nu, v = (1.0 + r) * nu;
-    auto other = [](double x) { return G == 8 ? dpp_f64<0x128>(x) : dpp_f64<0x141>(x); };   // row_ror:8, row_half_mirror
-    const double dp = (r - other(r)) * (1.0 / 3.0);
+    // outer minus inner probe (right in the outer probe's lanes): p = c_s^2 rho,
+    // tau = rho nu (grad u + grad u^T); grad u [i][j] = pp[1 + 3 i + j]
     double Ft[3], Mt[3] = {0, 0, 0};
+    const double nu = J.nu;
+    const double rp = 1.0 + pp[0], rm = 1.0 + pm[0];
+    const double dp = (pp[0] - pm[0]) * (1.0 / 3.0);
     for (int i = 0; i < 3; ++i) {
-        const double f = v * T[i];
-        Ft[i] = (f - other(f) - dp * nrm[i]) * (0.5 * ln);
+        double tn = 0.0;
+        for (int j = 0; j < 3; ++j)
+            tn += (rp * nu * (pp[1 + 3 * i + j] + pp[1 + 3 * j + i]) -
+                   rm * nu * (pm[1 + 3 * i + j] + pm[1 + 3 * j + i])) * nrm[j];
+        Ft[i] = (-dp * nrm[i] + tn) * A;
     }
     const bool store = live && side == 0 && lane == 0;
     if (store)
@@ -1095,11 +1054,11 @@ void launch_centroids(const Pools& P, int nblk_tri, int nblk_edge, bool fold, bo
     if (!(nblk_tri + nblk_edge > 0)) return;
     const dim3 grid(nblk_tri + nblk_edge), block(IB_BLOCK);
     if (P.solo_job >= 0) {
-        hipLaunchKernelGGL((k_centroids<true, 8, false>), grid, block, 0, s, P, nblk_tri, (int)fold);
-        if (wide) hipLaunchKernelGGL((k_centroids<true, 8, true>), dim3(nblk_tri), block, 0, s, P, nblk_tri, (int)fold);
+        hipLaunchKernelGGL((k_centroids<true, false>), grid, block, 0, s, P, nblk_tri, (int)fold);
+        if (wide) hipLaunchKernelGGL((k_centroids<true, true>), dim3(nblk_tri), block, 0, s, P, nblk_tri, (int)fold);
     } else {
-        hipLaunchKernelGGL((k_centroids<false, 8, false>), grid, block, 0, s, P, nblk_tri, (int)fold);
-        if (wide) hipLaunchKernelGGL((k_centroids<false, 8, true>), dim3(nblk_tri), block, 0, s, P, nblk_tri, (int)fold);
+        hipLaunchKernelGGL((k_centroids<false, false>), grid, block, 0, s, P, nblk_tri, (int)fold);
+        if (wide) hipLaunchKernelGGL((k_centroids<false, true>), dim3(nblk_tri), block, 0, s, P, nblk_tri, (int)fold);
     }
 }
 void launch_windows(const Pools& P, int nbodies, hipStream_t s) {
@@ -1113,11 +1072,11 @@ void launch_triangles(const Pools& P, int nblk_tri, int nblk_vel, bool wide, hip
     if (!(nblk_tri + nblk_vel > 0)) return;
     const dim3 grid(nblk_tri + nblk_vel), block(IB_BLOCK);
     if (P.solo_job >= 0) {
-        hipLaunchKernelGGL((k_triangles<true, 8, false>), grid, block, 0, s, P, nblk_tri);
-        if (wide) hipLaunchKernelGGL((k_triangles<true, 8, true>), grid, block, 0, s, P, nblk_tri);
+        hipLaunchKernelGGL((k_triangles<true, false>), grid, block, 0, s, P, nblk_tri);
+        if (wide) hipLaunchKernelGGL((k_triangles<true, true>), grid, block, 0, s, P, nblk_tri);
     } else {
-        hipLaunchKernelGGL((k_triangles<false, 8, false>), grid, block, 0, s, P, nblk_tri);
-        if (wide) hipLaunchKernelGGL((k_triangles<false, 8, true>), grid, block, 0, s, P, nblk_tri);
+        hipLaunchKernelGGL((k_triangles<false, false>), grid, block, 0, s, P, nblk_tri);
+        if (wide) hipLaunchKernelGGL((k_triangles<false, true>), grid, block, 0, s, P, nblk_tri);
     }
 }
 void launch_vertices(const Pools& P, int nblocks, hipStream_t s) {

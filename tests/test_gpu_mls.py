@@ -1,7 +1,6 @@
-"""The moving-least-squares form with 16 candidate nodes per point, against the rule it rests on
-(CPU) and against the FP64 oracle at the support radii, positions and windows where its choice of
-nodes or its index arithmetic could go wrong."""
-import itertools
+"""The moving-least-squares form that keeps only the nodes within the support radius: the count it
+rests on (CPU), and the step against the FP64 oracle at the radii, positions and windows where its
+choice of nodes or its index arithmetic could go wrong."""
 import os
 
 import numpy as np
@@ -10,31 +9,18 @@ import pytest
 from paper_2207_06029_amd import inputs as I
 
 
-def _candidates(f):
-    """The 8 corners of the cell around the point and the 7 far nodes; f = |x - nearest| per axis,
-    the point on the + side of its nearest node."""
-    near, second, far = 0, 1, -1
-    out = set(itertools.product((near, second), repeat=3))
-    for axes in itertools.chain.from_iterable(itertools.combinations(range(3), n) for n in (1, 2, 3)):
-        node = [near] * 3
-        for a in axes:
-            node[a] = second
-        node[min(axes, key=lambda a: f[a])] = far
-        out.add(tuple(node))
-    return out
-
-
-@pytest.mark.parametrize("rw", [0.9, 1.3, 1.378])
-def test_candidates_hold_every_support_node(rw):
+@pytest.mark.parametrize("rw", [0.9, 1.3, 1.378, 1.4])
+def test_lanes_never_hold_more_than_three_support_nodes(rw):
+    """Lane l of a point's eight owns nodes l, l + 8, ... of the 3x3x3 block; below r_w = sqrt(2) at
+    most two of those are within r_w for the lanes with four nodes (0, 1, 2) and for lane 5."""
     rng = np.random.default_rng(11)
-    pts = np.concatenate([rng.uniform(0.0, 0.5, (4000, 3)), rng.choice([0.0, 0.17, 0.25, 0.3, 0.5], (500, 3))])
-    block = list(itertools.product((-1, 0, 1), repeat=3))
-    for f in pts:
-        cand = _candidates(f)
-        assert len(cand) == 15
-        for n in block:
-            if sum((n[a] - f[a]) ** 2 for a in range(3)) <= rw * rw:
-                assert n in cand
+    pts = np.concatenate([rng.uniform(-0.5, 0.5, (20000, 3)), rng.choice([0.0, 0.15, -0.15, 0.45, -0.45, 0.5], (2000, 3))])
+    k = np.arange(27)
+    node = np.stack([k % 3 - 1, k // 3 % 3 - 1, k // 9 - 1], 1)
+    inside = ((node[None] - pts[:, None]) ** 2).sum(2) <= rw * rw
+    most = [inside[:, lane::8].sum(1).max() for lane in range(8)]
+    assert max(most) <= 3
+    assert max(most[lane] for lane in (0, 1, 2, 5)) <= 2
 
 
 @pytest.fixture(scope="module")
@@ -44,7 +30,7 @@ def api():
 
 
 CASES = {
-    # compact form: the usual radius, the largest below the bound, a point set on lattice symmetries
+    # three slots per lane: the usual radius, the largest below the bound, points on symmetries
     "rw1.3": dict(rw=1.3),
     "rw1.378": dict(rw=1.378),
     "on nodes": dict(rw=1.3, centre=(12.0, 12.0, 12.0)),
