@@ -253,8 +253,6 @@ void launch_sweep(const Pools& P, int storage, bool collide, bool a_to_b, int nt
                   hipEvent_t ev1 = nullptr);
 // nblk_w: total window blocks (each body gets blocks in proportion to its window capacity)
 void launch_window_moments(const Pools& P, int storage, bool from_b, int nblk_w, hipStream_t s);
-void launch_macros(const Pools& P, int storage, bool from_b, int job, long long n, float* out4,
-                   hipStream_t s);
 // rho[n] then u*[3n] in double (the host layout of lbib_get_macros), written to out[4n]
 void launch_macros_f64(const Pools& P, int storage, bool from_b, int job, long long n, double* out,
                        hipStream_t s);

