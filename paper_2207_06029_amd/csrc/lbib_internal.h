@@ -236,7 +236,7 @@ __device__ __forceinline__ void loaded(T&... v) { (..., [](auto& x) { asm volati
 struct SweepShape {
     int block;          // threads per block
     int npt;            // nodes per thread (block-strided)
-    int xcd_chunk;      // tiles an XCD takes per turn (0: dispatch order; -1: chosen by footprint)
+    int xcd_chunk;      // > 0: XCD_CHUNK tiles per XCD and turn; 0: dispatch order; -1: chosen by footprint
 };
 // Chunked XCD order pays while the two population buffers stay in the Infinity Cache (256 MB);
 // beyond it, dispatch order keeps all XCDs streaming the same region.

@@ -497,11 +497,14 @@ __device__ __forceinline__ void sweep_force(const Pools& P, const JobDev& J, con
     if (J.nbodies == 0) return;
     if (J.nbodies > 1) { node_force(P, J, x, y, z, F); return; }
     if (!W.valid) return;
-    int lx = x - W.o[0], ly = y - W.o[1], lz = z - W.o[2];
+    // z first: most waves of a lattice lie off the window's planes and leave here
+    int lz = z - W.o[2];
+    if (lz < 0) lz += J.nz;
+    if (lz >= W.w[2]) return;
+    int lx = x - W.o[0], ly = y - W.o[1];
     if (lx < 0) lx += J.nx;
     if (ly < 0) ly += J.ny;
-    if (lz < 0) lz += J.nz;
-    if (lx < W.w[0] && ly < W.w[1] && lz < W.w[2]) {
+    if (lx < W.w[0] && ly < W.w[1]) {
         const unsigned l = (unsigned)lx + (unsigned)W.w[0] * ((unsigned)ly + (unsigned)W.w[1] * (unsigned)lz);
         const long long* fw = W.fw + l;
         F[0] += (float)((double)fw[0] * FIX_INV);
@@ -635,9 +638,10 @@ __device__ __forceinline__ void sweep_node(const Pools& P, const JobDev& J, cons
             rw[1] = xorshift32(rw[0]);
 #pragma unroll
             for (int q = 0; q < 8; ++q) {
-                const int r = (int)(rw[q / 4] << (24 - 8 * (q % 4))) >> 24;   // -128..127
+                // a byte r in -128..127, read as r + 128 (one conversion instruction)
+                const unsigned r = ((rw[q / 4] ^ 0x80808080u) >> (8 * (q % 4))) & 255u;
                 // (r + 1/2) ulp / 256, exact (the step is a power of two)
-                dof[q] = fmaf((float)r, Narrow<S>::ulp * (1.f / 256.f), Narrow<S>::ulp * (0.5f / 256.f));
+                dof[q] = fmaf((float)r, Narrow<S>::ulp * (1.f / 256.f), Narrow<S>::ulp * (-127.5f / 256.f));
             }
 #pragma unroll
             for (int i = 0; i < Q; ++i) {
@@ -665,17 +669,22 @@ __device__ __forceinline__ void sweep_node(const Pools& P, const JobDev& J, cons
 // ONE: a batch of one lattice.  Its job (0) and body need no tile-table entry, so the job record,
 // the step counter and the force-window layout load at once, in parallel with the tile entry,
 // instead of one after the other at the start of every block.
+// Registers: the scalar ones bound the waves per SIMD too (800 per SIMD, in steps of 16), so the
+// compiler is held to 96 of them: eight waves instead of seven (64-job FP16 batch 664 -> 642 us per
+// step).  The 16-bit sweep of one lattice, the one with the most vector work per byte, is also
+// scheduled for eight waves (96x96x384 51.6 -> 49.1 us); FP32 lost 0.5 % by that, and the batched
+// 16-bit form spilled scalars (918 us).
 template <typename S, bool COLLIDE, int NPT, bool OFF32, bool ONE>
-__global__ void __launch_bounds__(1024) k_sweep(Pools P, int a_to_b, int xcd_chunk) {
+__global__ void __launch_bounds__(1024, ONE && sizeof(S) == 2 ? 8 : 4) __attribute__((amdgpu_num_sgpr(96))) k_sweep(Pools P, int a_to_b, int xcd_chunk) {
     // The dispatcher deals consecutive blocks to the 8 XCDs in turn, each with its own L2.
-    // With xcd_chunk = C > 0 the blocks are remapped so that every XCD takes C consecutive
+    // With xcd_chunk set the blocks are remapped so that every XCD takes C = XCD_CHUNK consecutive
     // tiles per turn: the rows a tile pulls from its neighbours were mostly just read through
     // the same L2.  Blocks past the last whole turn keep their own tile (a bijection).
-    const int T = gridDim.x, bid = blockIdx.x;
+    const unsigned T = gridDim.x, bid = blockIdx.x;
     int tile = bid;
     if (xcd_chunk > 0) {
-        const int span = 8 * xcd_chunk;
-        if (bid < (T / span) * span) tile = (bid / span) * span + (bid & 7) * xcd_chunk + (bid >> 3) % xcd_chunk;
+        constexpr int C = XCD_CHUNK, span = 8 * C;
+        if (bid < T / span * span) tile = bid / span * span + (bid & 7) * C + (bid >> 3) % C;
     }
     const int4 te = P.tiles[tile];
     const int job = ONE ? 0 : te.x;
