@@ -21,7 +21,7 @@
 //                partial force and torque per block.  Blocks of their own: the fluid velocity
 //                at every membrane vertex from f^{n+1}
 //   k_fold_bodies (rigid bodies) FP64 totals and the velocity / pose update
-//   k_vertices   gathered forces, membrane update with that velocity, integer bounding box
+//   k_vertices   gathered forces, membrane update with that velocity, integer bounding boxes
 //                of x^{n+1} for the next step's window
 #include "lbib_internal.h"
 
@@ -61,8 +61,9 @@ __device__ __forceinline__ void gsum8(double v[K]) {
     for (int i = 0; i < K; ++i) v[i] += dpp_f64<0x141>(v[i]);
 }
 
-// Minimum / maximum over the wave: DPP within rows (quad permutes, half-mirror, mirror), then
-// two lane exchanges across rows.  Every lane ends with the result.
+// Minimum / maximum over the wave: DPP within rows (quad permutes, half-mirror, mirror), then the
+// four rows from scalar registers, where the result stays: what is derived from it (the spreading
+// box, the force window) is then scalar work too.
 template <int CTRL>
 __device__ __forceinline__ int dpp_i32(int v) {
     return __builtin_amdgcn_mov_dpp(v, CTRL, 0xF, 0xF, true);
@@ -74,9 +75,8 @@ __device__ __forceinline__ int wave_minmax(int v) {
     v = op(v, dpp_i32<0x4E>(v));
     v = op(v, dpp_i32<0x141>(v));
     v = op(v, dpp_i32<0x140>(v));
-    v = op(v, __shfl_xor(v, 16, 64));
-    v = op(v, __shfl_xor(v, 32, 64));
-    return v;
+    return op(op(__builtin_amdgcn_readlane(v, 0), __builtin_amdgcn_readlane(v, 16)),
+              op(__builtin_amdgcn_readlane(v, 32), __builtin_amdgcn_readlane(v, 48)));
 }
 
 
@@ -436,39 +436,34 @@ __device__ __forceinline__ long long fix_rn(double v, bool& small) {
 // planes; a block whose box exceeds 8 x 8 x SPREAD_LDS_Z (markers far apart on the lattice) adds
 // straight to global memory.
 //
-// With fold set, the same block-wide reduction also folds the integer boxes that the vertex
-// blocks wrote for x^n into this step's force window (min / max, order independent): every
-// block derives the same descriptor and block 0 publishes it for the sweep and the moments.
-// vb[6] is the box of the vertex-block boxes this thread loaded.
-// Without fold, fd_in is the window the window kernel of the previous step published.
+// The same block-wide reduction also folds the integer boxes that the vertex blocks wrote for x^n
+// into this step's force window (min / max, order independent): every block derives the same
+// descriptor and block 0 publishes it for the sweep and the moments.  vb[6] is the box of the
+// vertex-block boxes this thread loaded.  Folding once per body in a kernel of its own saved the
+// 64-job batch's 30,000 blocks as much as its launch cost (644 us per step either way), and cost
+// smaller launches the launch: 12 jobs 86.3 -> 83.2 us, four capsules in one lattice 42.8 -> 41.1.
 constexpr int SPREAD_LDS_Z = 6;
 
 template <bool WIDE>
 __device__ __forceinline__ void spread_block(const Pools& P, const JobDev& J, const BodyDev& B, int b,
-                                             int blk, bool fold, const int vb[6], const WinDesc& fd_in,
-                                             bool live, MlsLane<WIDE>& m,
+                                             int blk, const int vb[6], bool live, MlsLane<WIDE>& m,
                                              const long long fx[MlsLane<WIDE>::N][3], int& err) {
     constexpr int N = MlsLane<WIDE>::N;
     static_assert(IB_BLOCK == 64, "the block is one wave: its boxes are wave reductions");
     __shared__ unsigned long long s_acc[3][64 * SPREAD_LDS_Z];
     const long long capn = (long long)B.win_cap[0] * B.win_cap[1] * B.win_cap[2];
     unsigned long long* fw0 = (unsigned long long*)(P.fwin + 3 * B.win_off);
-    // stencil box of the block's markers; with fold, the box of the vertex-block boxes
+    // stencil box of the block's markers, and the box of the vertex-block boxes
     int o[3], w[3], bmin[3], bmax[3];
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
         o[a] = wave_minmax<false>(m.c[a]) - 1;
         w[a] = wave_minmax<true>(m.c[a]) + 2 - o[a];
-        if (fold) {
-            bmin[a] = wave_minmax<false>(vb[a]);
-            bmax[a] = wave_minmax<true>(vb[3 + a]);
-        }
+        bmin[a] = wave_minmax<false>(vb[a]);
+        bmax[a] = wave_minmax<true>(vb[3 + a]);
     }
-    WinDesc fd = fd_in;
-    if (fold) {
-        fd = window_from_box(J, B, bmin, bmax, err);
-        if (blk == 0 && threadIdx.x == 0) P.fdesc[b] = fd;
-    }
+    const WinDesc fd = window_from_box(J, B, bmin, bmax, err);
+    if (blk == 0 && threadIdx.x == 0) P.fdesc[b] = fd;
     const bool use_lds = w[0] <= 8 && w[1] <= 8 && w[2] <= SPREAD_LDS_Z;   // uniform over the block
     unsigned idx[N];
     if (!use_lds) {
@@ -526,7 +521,7 @@ __device__ __forceinline__ void spread_block(const Pools& P, const JobDev& J, co
 
 // ---------------------------------------------------------------- centroids (+ hinges)
 template <bool SOLO, bool WIDE>
-__global__ void __launch_bounds__(IB_BLOCK, SOLO ? 1 : 4) k_centroids(Pools P, int nblk_tri, int fold) {
+__global__ void __launch_bounds__(IB_BLOCK, SOLO ? 1 : 4) k_centroids(Pools P, int nblk_tri) {
     constexpr int N = MlsLane<WIDE>::N, PTS = IB_BLOCK / MLS_GROUP;
     if ((int)blockIdx.x >= nblk_tri) {
         // edge blocks: one thread per hinge of a membrane
@@ -552,19 +547,12 @@ __global__ void __launch_bounds__(IB_BLOCK, SOLO ? 1 : 4) k_centroids(Pools P, i
     const int t = live ? blk * PTS + grp : B.nt - 1;   // a spare group repeats the last triangle
     int err = 0;
     // everything this block reads before its MLS work is loaded first, so that the latencies
-    // overlap: the vertex-block boxes of x^n (fold) or the published window, the triangle's
-    // vertices and the desired-velocity inputs
+    // overlap: the vertex-block boxes of x^n, the triangle's vertices and the desired-velocity inputs
     int vb[6] = {0x7fffffff, 0x7fffffff, 0x7fffffff, -0x7fffffff, -0x7fffffff, -0x7fffffff};
-    WinDesc fd_pub = {};
     const WinDesc md = P.mdesc[b];
-    if (fold) {
-        // every vertex-block box, loaded now so that these loads overlap the MLS work
-        for (int q = threadIdx.x; q < B.nblk_v; q += blockDim.x) {
-            const int* e = P.vbox + 6LL * (B.vbox0 + q);
-            for (int a = 0; a < 3; ++a) { vb[a] = min(vb[a], e[a]); vb[3 + a] = max(vb[3 + a], e[3 + a]); }
-        }
-    } else {
-        fd_pub = P.fdesc[b];
+    for (int q = threadIdx.x; q < B.nblk_v; q += blockDim.x) {
+        const int* e = P.vbox + 6LL * (B.vbox0 + q);
+        for (int a = 0; a < 3; ++a) { vb[a] = min(vb[a], e[a]); vb[3 + a] = max(vb[3 + a], e[3 + a]); }
     }
     double xa[3], xb_[3], xc[3], Ub[3] = {0, 0, 0};
     const int* tv = P.tri + 3 * (B.t0 + t);
@@ -628,7 +616,7 @@ __global__ void __launch_bounds__(IB_BLOCK, SOLO ? 1 : 4) k_centroids(Pools P, i
         MLS_SLOTS(s, m)
             for (int a = 0; a < 3; ++a) fx[s][a] = __double2ll_rn(fs * m.phi[s] * U[a]);
     }
-    spread_block<WIDE>(P, J, B, b, blk, fold != 0, vb, fd_pub, live, m, fx, err);
+    spread_block<WIDE>(P, J, B, b, blk, vb, live, m, fx, err);
     if (err && live) atomicOr(P.flags + B.job, err);
     if (B.rigid || B.kv == 0.0) return;
     // one partial of the volume per VOL_GROUP triangles, folded into V by k_fold_bodies
@@ -977,38 +965,6 @@ __global__ void __launch_bounds__(VERT_BLOCK) k_vertices(Pools P) {
     }
 }
 
-// ---------------------------------------------------------------- windows of the next step
-// One block per body: fold the integer boxes of x^{n+1} the vertex blocks wrote and publish the
-// force window of the next step (used for batches, where folding once per body is cheaper than
-// once per centroid block).
-__global__ void __launch_bounds__(256) k_windows(Pools P) {
-    const int b = blockIdx.x;
-    const BodyDev& B = P.bodies[b];
-    if (B.nv == 0) return;   // an empty slot of a slotted batch
-    const JobDev& J = P.jobs[B.job];
-    __shared__ int red[6][256];
-    const int t = threadIdx.x;
-    int e[6] = {0x7fffffff, 0x7fffffff, 0x7fffffff, -0x7fffffff, -0x7fffffff, -0x7fffffff};
-    for (int q = t; q < B.nblk_v; q += 256) {
-        const int* vb = P.vbox + 6LL * (B.vbox0 + q);
-        for (int a = 0; a < 3; ++a) { e[a] = min(e[a], vb[a]); e[3 + a] = max(e[3 + a], vb[3 + a]); }
-    }
-    for (int a = 0; a < 6; ++a) red[a][t] = e[a];
-    __syncthreads();
-    for (int w = 128; w >= 1; w >>= 1) {
-        if (t < w)
-            for (int a = 0; a < 6; ++a)
-                red[a][t] = a < 3 ? min(red[a][t], red[a][t + w]) : max(red[a][t], red[a][t + w]);
-        __syncthreads();
-    }
-    if (t == 0) {
-        int err = 0;
-        const int bmin[3] = {red[0][0], red[1][0], red[2][0]}, bmax[3] = {red[3][0], red[4][0], red[5][0]};
-        P.fdesc[b] = window_from_box(J, B, bmin, bmax, err);
-        if (err) atomicOr(P.flags + B.job, err);
-    }
-}
-
 // ---------------------------------------------------------------- reported totals (membranes)
 // FP64 hydrodynamic force and torque of the last step, torque about the vertex mean of x^n
 // (held in xprev after the update).  One block, fixed-shape tree: reproducible.
@@ -1050,19 +1006,16 @@ __global__ void __launch_bounds__(256) k_body_totals(Pools P, int b, double* out
 
 // A launch in the compact form and, where a body's support needs it, one in the WIDE form: each
 // serves the bodies of its form.  The edge blocks ride in the first.
-void launch_centroids(const Pools& P, int nblk_tri, int nblk_edge, bool fold, bool wide, hipStream_t s) {
+void launch_centroids(const Pools& P, int nblk_tri, int nblk_edge, bool wide, hipStream_t s) {
     if (!(nblk_tri + nblk_edge > 0)) return;
     const dim3 grid(nblk_tri + nblk_edge), block(IB_BLOCK);
     if (P.solo_job >= 0) {
-        hipLaunchKernelGGL((k_centroids<true, false>), grid, block, 0, s, P, nblk_tri, (int)fold);
-        if (wide) hipLaunchKernelGGL((k_centroids<true, true>), dim3(nblk_tri), block, 0, s, P, nblk_tri, (int)fold);
+        hipLaunchKernelGGL((k_centroids<true, false>), grid, block, 0, s, P, nblk_tri);
+        if (wide) hipLaunchKernelGGL((k_centroids<true, true>), dim3(nblk_tri), block, 0, s, P, nblk_tri);
     } else {
-        hipLaunchKernelGGL((k_centroids<false, false>), grid, block, 0, s, P, nblk_tri, (int)fold);
-        if (wide) hipLaunchKernelGGL((k_centroids<false, true>), dim3(nblk_tri), block, 0, s, P, nblk_tri, (int)fold);
+        hipLaunchKernelGGL((k_centroids<false, false>), grid, block, 0, s, P, nblk_tri);
+        if (wide) hipLaunchKernelGGL((k_centroids<false, true>), dim3(nblk_tri), block, 0, s, P, nblk_tri);
     }
-}
-void launch_windows(const Pools& P, int nbodies, hipStream_t s) {
-    if (nbodies > 0) hipLaunchKernelGGL(k_windows, dim3(nbodies), dim3(256), 0, s, P);
 }
 void launch_fold_bodies(const Pools& P, int nbodies, int mode, hipStream_t s) {
     if (nbodies > 0) hipLaunchKernelGGL(k_fold_bodies, dim3(nbodies), dim3(FOLD_THREADS), 0, s, P, mode);

@@ -267,13 +267,8 @@ void launch_init_eq(const Pools& P, int storage, bool to_b, int job, long long n
                     const double* u, hipStream_t s);
 
 // lbib_ib.hip
-// fold: the centroid blocks derive this step's force window from the vertex-block boxes
-// themselves; otherwise launch_windows after the vertex kernel has published it.
 // wide: some body's MLS support needs all 27 nodes around a point.
-void launch_centroids(const Pools& P, int nblk_tri, int nblk_edge, bool fold, bool wide, hipStream_t s);
-void launch_windows(const Pools& P, int nbodies, hipStream_t s);
-// bodies from which the force windows are folded once per body by a kernel of their own
-constexpr int WINDOW_KERNEL_MIN_BODIES = 2;
+void launch_centroids(const Pools& P, int nblk_tri, int nblk_edge, bool wide, hipStream_t s);
 void launch_triangles(const Pools& P, int nblk_tri, int nblk_vel, bool wide, hipStream_t s);
 // mode 0: volumes of membranes with a volume penalty; mode 1: rigid totals and pose update
 void launch_fold_bodies(const Pools& P, int nbodies, int mode, hipStream_t s);

@@ -826,9 +826,8 @@ lbib_status Batch::prime() {
 
 lbib_status Batch::enqueue_step(bool collide) {
     const bool bodies = collide && nbodies > 0;
-    const bool fold_once = nbodies >= WINDOW_KERNEL_MIN_BODIES;
     if (bodies) {
-        launch_centroids(P, nblk_c, nblk_e, !fold_once, any_wide, stream);
+        launch_centroids(P, nblk_c, nblk_e, any_wide, stream);
         if (any_volume) launch_fold_bodies(P, nbodies, 0, stream);
     }
     if (timing && sweep_seq++ % timing_period == 0) {
@@ -847,7 +846,6 @@ lbib_status Batch::enqueue_step(bool collide) {
         launch_triangles(P, nblk_t, nblk_u, any_wide, stream);
         if (any_rigid) launch_fold_bodies(P, nbodies, 1, stream);
         launch_vertices(P, nblk_v, stream);
-        if (fold_once) launch_windows(P, nbodies, stream);
     }
     HIP_TRY(hipGetLastError());
     return LBIB_OK;
@@ -1155,7 +1153,6 @@ lbib_status Batch::create_slotted(int nslots, const SlotCaps& c, int storage_, v
         host_bodies[j].job = j;
     }
     P.solo_job = -1;
-    any_rigid = any_volume = true;   // the fold launches skip bodies without that work
     use_graph = false;
     primed = true;   // admissions prime their own moment windows
     lbib_status r = slot_tables();
@@ -1170,7 +1167,7 @@ lbib_status Batch::slot_tables() {
     const int S = (int)slot_live.size();
     const long long per = (long long)shape.block * shape.npt;
     tiles.clear();
-    any_wide = false;
+    any_rigid = any_volume = any_wide = false;
     std::vector<int> bc, be, bt, bv, bu, bw;
     for (int s = 0; s < S; ++s) {
         JobDev& J = jobs[s];
@@ -1187,6 +1184,8 @@ lbib_status Batch::slot_tables() {
         }
         if (B.nv == 0) continue;
         if (B.rw2 >= MLS_COMPACT_RW2) any_wide = true;
+        if (B.rigid) any_rigid = true;
+        else if (B.kv != 0.0) any_volume = true;
         const int nbc = (B.nt + MLS_PER_BLOCK - 1) / MLS_PER_BLOCK, nbt = (B.nt + TRI_PER_BLOCK - 1) / TRI_PER_BLOCK;
         const int nbu = (B.nv + MLS_PER_BLOCK - 1) / MLS_PER_BLOCK, nbv = (B.nv + VERT_PER_BLOCK - 1) / VERT_PER_BLOCK;
         const int nbe = B.rigid ? 0 : (B.ne + IB_BLOCK - 1) / IB_BLOCK;
