@@ -443,6 +443,8 @@ __device__ __forceinline__ long long fix_rn(double v, bool& small) {
 // 64-job batch's 30,000 blocks as much as its launch cost (644 us per step either way), and cost
 // smaller launches the launch: 12 jobs 86.3 -> 83.2 us, four capsules in one lattice 42.8 -> 41.1.
 constexpr int SPREAD_LDS_Z = 6;
+// vertex-block boxes a lone body's centroid blocks load ahead (a level-4 icosphere has 161)
+template <bool SOLO> constexpr int vbox_early() { return SOLO ? 3 * IB_BLOCK : IB_BLOCK; }
 
 template <bool WIDE>
 __device__ __forceinline__ void spread_block(const Pools& P, const JobDev& J, const BodyDev& B, int b,
@@ -522,7 +524,7 @@ __device__ __forceinline__ void spread_block(const Pools& P, const JobDev& J, co
 // ---------------------------------------------------------------- centroids (+ hinges)
 template <bool SOLO, bool WIDE>
 __global__ void __launch_bounds__(IB_BLOCK, SOLO ? 1 : 4) k_centroids(Pools P, int nblk_tri) {
-    constexpr int N = MlsLane<WIDE>::N, PTS = IB_BLOCK / MLS_GROUP;
+    constexpr int N = MlsLane<WIDE>::N, PTS = IB_BLOCK / MLS_GROUP, VBOX_EARLY = vbox_early<SOLO>();
     if ((int)blockIdx.x >= nblk_tri) {
         // edge blocks: one thread per hinge of a membrane
         const int eb = blockIdx.x - nblk_tri;
@@ -540,20 +542,19 @@ __global__ void __launch_bounds__(IB_BLOCK, SOLO ? 1 : 4) k_centroids(Pools P, i
     const BodyDev& B = body_of<SOLO>(P, b);
     if ((B.rw2 >= MLS_COMPACT_RW2) != WIDE) return;   // the other form's launch
     const JobDev J = body_job<SOLO>(P, B);   // copied before the first store: one round of scalar loads
+    const WinDesc md = P.mdesc[b];
     BodyState& S = P.bstate[b];
     const int grp = threadIdx.x / MLS_GROUP, lane = threadIdx.x % MLS_GROUP;
     const int blk = blockIdx.x - B.blk_c0;
+    if (SOLO)
+        loaded(P.tri, P.x, P.uv, P.vbox, P.mwin, P.fwin, P.tgeo, B.nt, B.t0, B.v0, B.win_off, B.win_cap[0], B.win_cap[2],
+               B.nblk_v, B.vbox0, B.rigid, B.kv, B.shell_h, B.wq, J.nx, J.ny, J.nz, J.bc[0], J.bc[2], J.bc[4], md.w[0],
+               md.w[1], md.w[2], md.b[0], md.b[1], md.b[2]);
     const bool live = blk * PTS + grp < B.nt;
     const int t = live ? blk * PTS + grp : B.nt - 1;   // a spare group repeats the last triangle
     int err = 0;
     // everything this block reads before its MLS work is loaded first, so that the latencies
     // overlap: the vertex-block boxes of x^n, the triangle's vertices and the desired-velocity inputs
-    int vb[6] = {0x7fffffff, 0x7fffffff, 0x7fffffff, -0x7fffffff, -0x7fffffff, -0x7fffffff};
-    const WinDesc md = P.mdesc[b];
-    for (int q = threadIdx.x; q < B.nblk_v; q += blockDim.x) {
-        const int* e = P.vbox + 6LL * (B.vbox0 + q);
-        for (int a = 0; a < 3; ++a) { vb[a] = min(vb[a], e[a]); vb[3 + a] = max(vb[3 + a], e[3 + a]); }
-    }
     double xa[3], xb_[3], xc[3], Ub[3] = {0, 0, 0};
     const int* tv = P.tri + 3 * (B.t0 + t);
     load3(P.x + 3 * (B.v0 + tv[0]), xa);
@@ -563,6 +564,15 @@ __global__ void __launch_bounds__(IB_BLOCK, SOLO ? 1 : 4) k_centroids(Pools P, i
         for (int a = 0; a < 3; ++a)
             Ub[a] = (P.uv[3 * (B.v0 + tv[0]) + a] + P.uv[3 * (B.v0 + tv[1]) + a] +
                      P.uv[3 * (B.v0 + tv[2]) + a]) * (1.0 / 3.0);
+    // boxes of the first VBOX_EARLY vertex blocks, held until the force window needs them (a box past
+    // the last one repeats it)
+    const int* box = P.vbox + 6LL * B.vbox0;
+    int eb[VBOX_EARLY / IB_BLOCK][6];
+#pragma unroll
+    for (int i = 0; i < VBOX_EARLY / IB_BLOCK; ++i) {
+        const int q = min(IB_BLOCK * i + (int)threadIdx.x, B.nblk_v - 1);
+        for (int a = 0; a < 6; ++a) eb[i][a] = box[6 * q + a];
+    }
     double cen[3], ab[3], ac[3], nn[3];
     for (int a = 0; a < 3; ++a) {
         cen[a] = (xa[a] + xb_[a] + xc[a]) * (1.0 / 3.0);
@@ -616,6 +626,22 @@ __global__ void __launch_bounds__(IB_BLOCK, SOLO ? 1 : 4) k_centroids(Pools P, i
         MLS_SLOTS(s, m)
             for (int a = 0; a < 3; ++a) fx[s][a] = __double2ll_rn(fs * m.phi[s] * U[a]);
     }
+    int vb[6];
+    for (int a = 0; a < 6; ++a) vb[a] = eb[0][a];
+#pragma unroll
+    for (int i = 1; i < VBOX_EARLY / IB_BLOCK; ++i)
+        for (int a = 0; a < 3; ++a) { vb[a] = min(vb[a], eb[i][a]); vb[3 + a] = max(vb[3 + a], eb[i][3 + a]); }
+    for (int q0 = VBOX_EARLY; q0 < B.nblk_v; q0 += 4 * IB_BLOCK) {
+        int e[4][6];   // four boxes in flight per lane
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int q = min(q0 + IB_BLOCK * i + (int)threadIdx.x, B.nblk_v - 1);
+            for (int a = 0; a < 6; ++a) e[i][a] = box[6 * q + a];
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            for (int a = 0; a < 3; ++a) { vb[a] = min(vb[a], e[i][a]); vb[3 + a] = max(vb[3 + a], e[i][3 + a]); }
+    }
     spread_block<WIDE>(P, J, B, b, blk, vb, live, m, fx, err);
     if (err && live) atomicOr(P.flags + B.job, err);
     if (B.rigid || B.kv == 0.0) return;
@@ -643,13 +669,16 @@ __device__ void vertex_velocity_block(const Pools& P, int vb) {
     const BodyDev& B = body_of<SOLO>(P, b);
     if (B.rigid || (B.rw2 >= MLS_COMPACT_RW2) != WIDE) return;
     const JobDev J = body_job<SOLO>(P, B);
+    const WinDesc md = P.mdesc[b];
+    if (SOLO)
+        loaded(P.x, P.mwin, B.nv, B.v0, B.win_off, B.wq, J.nx, J.ny, J.nz, J.bc[0], J.bc[2], J.bc[4], md.w[0], md.w[1],
+               md.w[2], md.b[0], md.b[1], md.b[2]);
     const int grp = threadIdx.x / MLS_GROUP, lane = threadIdx.x % MLS_GROUP;
     const bool live = (vb - B.blk_u0) * PTS + grp < B.nv;
     const long long gv = B.v0 + (live ? (vb - B.blk_u0) * PTS + grp : B.nv - 1);
     int err = 0;
     double x[3];
     load3(P.x + 3 * gv, x);
-    const WinDesc md = P.mdesc[b];
     MlsLane<WIDE> m;
     unsigned idx[N];
     float4 mom[N];
@@ -678,13 +707,16 @@ __global__ void __launch_bounds__(IB_BLOCK, 4) k_triangles(Pools P, int nblk_tri
     const BodyDev& B = body_of<SOLO>(P, b);
     if ((B.rw2 >= MLS_COMPACT_RW2) != WIDE) return;   // the other form's launch
     const JobDev J = body_job<SOLO>(P, B);   // copied before the first store: one round of scalar loads
+    const WinDesc md = P.mdesc[b];
     BodyState& S = P.bstate[b];
     const int grp = threadIdx.x / MLS_GROUP, lane = threadIdx.x % MLS_GROUP;
     const int blk = blockIdx.x - B.blk_t0;
+    if (SOLO)
+        loaded(P.tgeo, P.mwin, P.fext, P.fvol, B.nt, B.t0, B.win_off, B.probe, B.rigid, B.kv, B.wq, J.nx, J.ny, J.nz,
+               J.nu, J.bc[0], J.bc[2], J.bc[4], md.w[0], md.w[1], md.w[2], md.b[0], md.b[1], md.b[2]);
     const int k = grp >> 1, side = grp & 1;
     const bool live = blk * TRIS + k < B.nt;
     const int t = live ? blk * TRIS + k : B.nt - 1;   // spare groups repeat the last triangle
-    const WinDesc md = P.mdesc[b];
     int err = 0;
     // centroid and normal at x^n, as the centroid kernel of this step computed them
     const double* g = P.tgeo + 6 * (B.t0 + t);
@@ -855,6 +887,9 @@ __global__ void __launch_bounds__(VERT_BLOCK) k_vertices(Pools P) {
     const int grp = threadIdx.x / VERT_GROUP, lane = threadIdx.x % VERT_GROUP;
     const int blk = blockIdx.x - B.blk_v0;
     const int v = blk * VERT_PER_BLOCK + grp;
+    if (SOLO)
+        loaded(P.vt_list, P.vh_list, P.x, P.u0v, P.fext, P.fvol, P.fedge, P.xprev, P.uv, P.fv, P.vbox, B.nv, B.v0, B.t0,
+               B.e0, B.vt_off, B.vh_off, B.vt_w, B.vh_w, B.rigid, B.integrator, B.mv, B.vbox0);
     __shared__ int box[VERT_PER_BLOCK][6];
     int err = 0;
     int bl[3] = {0x7fffffff, 0x7fffffff, 0x7fffffff}, bh[3] = {-0x7fffffff, -0x7fffffff, -0x7fffffff};

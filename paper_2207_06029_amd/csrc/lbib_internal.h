@@ -226,11 +226,11 @@ __device__ __forceinline__ const JobDev& body_job(const Pools& P, const BodyDev&
     return P.jobs[SOLO ? P.solo_job : B.job];
 }
 
-// Make a value loaded from a table available here, in scalar registers.  Uniform loads otherwise
-// stay behind the branches before their uses, one dependent round trip beyond the L2 each, which is
-// what short launches spend their time on.
+// Have values of the kernel arguments and tables in scalar registers here.  The compiler otherwise
+// leaves uniform loads behind the branches before their uses: a dependent round trip beyond the
+// scalar cache each, and a short launch consists of little else.
 template <typename... T>
-__device__ __forceinline__ void loaded(T&... v) { (..., [](auto& x) { asm volatile("" : "+s"(x)); }(v)); }
+__device__ __forceinline__ void loaded(const T&... v) { (..., [](const auto& x) { asm volatile("" ::"s"(x)); }(v)); }
 
 // ---------------------------------------------------------------- launchers
 struct SweepShape {
