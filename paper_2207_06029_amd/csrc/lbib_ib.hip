@@ -13,9 +13,9 @@
 //                geometry at x^n (kept for the probes), MLS at centroids on moments of f^n,
 //                F_l = U_b - U*, fixed-point spreading into the body's force window, partial
 //                enclosed volumes; edge blocks: spring and bending forces of every hinge
-//   k_fold_bodies (membranes with k_v != 0) volume V^n from the partials
 //   (sweep)      collide+stream with the spread force
-//   (moments)    moments of f^{n+1} in the body's window
+//   (moments)    moments of f^{n+1} in the body's window; a block per body for the volume V^n of
+//                membranes with k_v != 0 from the partials
 //   k_triangles  one group per probe (geometry from the centroid kernel): stresses on f^{n+1}
 //                (Eqs. hydroForP, hydroForNu), volume force per triangle; rigid bodies: FP64
 //                partial force and torque per block.  Blocks of their own: the fluid velocity
@@ -23,31 +23,9 @@
 //   k_fold_bodies (rigid bodies) FP64 totals and the velocity / pose update
 //   k_vertices   gathered forces, membrane update with that velocity, integer bounding boxes
 //                of x^{n+1} for the next step's window
-#include "lbib_internal.h"
+#include "lbib_reduce.h"
 
 namespace lbib {
-
-template <int CTRL>
-__device__ __forceinline__ double dpp_f64(double v) {
-    // every control used here reads a valid lane, so no value for the others is set up
-    const int lo = __builtin_amdgcn_mov_dpp(__double2loint(v), CTRL, 0xF, 0xF, true);
-    const int hi = __builtin_amdgcn_mov_dpp(__double2hiint(v), CTRL, 0xF, 0xF, true);
-    return __hiloint2double(hi, lo);
-}
-// Sum over a group of G = 8 (half a DPP row) or 16 lanes (a row).  Lane exchanges xor 1 and xor 2
-// are quad permutes, then the row half-mirror pairs the two quads of 8 lanes and the row mirror
-// the two halves of a row (after the previous levels every lane of a block holds the same
-// partial, so a mirror acts as an exchange).  Each level adds the same two operands on both
-// partners, so every lane ends with the identical sum, and no value leaves the group.
-template <int G>
-__device__ __forceinline__ double gsum(double v) {
-    static_assert(G == 8 || G == 16, "groups of 8 or 16 lanes");
-    v += dpp_f64<0xB1>(v);   // quad_perm [1,0,3,2]
-    v += dpp_f64<0x4E>(v);   // quad_perm [2,3,0,1]
-    v += dpp_f64<0x141>(v);  // row_half_mirror
-    if (G == 16) v += dpp_f64<0x140>(v);  // row_mirror
-    return v;
-}
 
 // The same for K values, level by level: a DPP move reads its operand two cycles after it was
 // written at the earliest, and the other values' additions fill that time.
@@ -276,69 +254,6 @@ __device__ __forceinline__ void cross3(const double a[3], const double b[3], dou
 }
 __device__ __forceinline__ double dot3(const double a[3], const double b[3]) {
     return a[0] * b[0] + a[1] * b[1] + a[2] * b[2];
-}
-
-// Deterministic per-body totals.  Every block of a body stores its partial sums (up to six
-// values, one row per value in the body's region); one block per body folds them in a later
-// launch, whose boundary makes the partials visible without a per-block device-scope release
-// (each of which would write back an L2).  Thread t takes blocks t, t+512, ... in order, then a
-// fixed tree (DPP within each wave, the eight waves in order) combines the 512 results: the
-// order depends only on the body's own block count, so totals are bitwise reproducible and
-// independent of other jobs in the launch.
-constexpr int FOLD_MAX = 6;
-constexpr int FOLD_THREADS = 512;   // threads of the fold block: 2048 partials per load round
-
-// A body's partials: value i of block k at 16 red_slot + i stride + k, stride = the body's larger
-// block count (its region holds 16 such rows), so a wave of the fold reads value i of 64
-// consecutive blocks from consecutive addresses.
-__device__ __forceinline__ long long partial_stride(const BodyDev& B) { return max(B.nblk_c, B.nblk_t); }
-__device__ __forceinline__ void store_partials(const Pools& P, const BodyDev& B, int blk, const double* v,
-                                               int nval) {
-    double* row = P.partial + 16LL * B.red_slot + blk;
-    const long long st = partial_stride(B);
-    for (int i = 0; i < nval; ++i) row[i * st] = v[i];
-}
-
-template <int NVAL>
-__device__ void fold_partials(const Pools& P, const BodyDev& B, int nblk, double* out) {
-    __shared__ double s_red[FOLD_MAX][FOLD_THREADS / 64];
-    const int t = threadIdx.x;
-    double acc[NVAL];
-    for (int i = 0; i < NVAL; ++i) acc[i] = 0.0;
-    // four slots per round, loaded together; summed in ascending block order
-    const double* rows = P.partial + 16LL * B.red_slot;
-    const long long st = partial_stride(B);
-    for (int k0 = t; k0 < nblk; k0 += 4 * FOLD_THREADS) {
-        double v[4][NVAL];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const int k = k0 + u * FOLD_THREADS;
-            const double* col = rows + (k < nblk ? k : 0);
-#pragma unroll
-            for (int i = 0; i < NVAL; ++i) v[u][i] = col[i * st];
-        }
-#pragma unroll
-        for (int u = 0; u < 4; ++u)
-            if (k0 + u * FOLD_THREADS < nblk)
-#pragma unroll
-                for (int i = 0; i < NVAL; ++i) acc[i] += v[u][i];
-    }
-    // each wave sums its 64 lanes (rows by DPP, then the four rows by two exchanges), wave 0's
-    // first lane adds the waves in order: a fixed tree, so the totals are reproducible
-    const int wave = t / 64, lane = t % 64;
-#pragma unroll
-    for (int i = 0; i < NVAL; ++i) {
-        double v = gsum<16>(acc[i]);
-        v += __shfl_xor(v, 16, 64);
-        v += __shfl_xor(v, 32, 64);
-        if (lane == 0) s_red[i][wave] = v;
-    }
-    __syncthreads();
-    for (int i = 0; i < NVAL; ++i) {
-        double v = s_red[i][0];
-        for (int w = 1; w < FOLD_THREADS / 64; ++w) v += s_red[i][w];
-        out[i] = v;
-    }
 }
 
 // ---------------------------------------------------------------- window of a step
@@ -645,7 +560,7 @@ __global__ void __launch_bounds__(IB_BLOCK, SOLO ? 1 : 4) k_centroids(Pools P, i
     spread_block<WIDE>(P, J, B, b, blk, vb, live, m, fx, err);
     if (err && live) atomicOr(P.flags + B.job, err);
     if (B.rigid || B.kv == 0.0) return;
-    // one partial of the volume per VOL_GROUP triangles, folded into V by k_fold_bodies
+    // one partial of the volume per VOL_GROUP triangles, folded into V by the moments launch
     __shared__ double vol[PTS];
     if (lane == 0) vol[grp] = live ? Vt : 0.0;
     __syncthreads();
@@ -854,19 +769,15 @@ __device__ bool rigid_update(const BodyDev& B, BodyState& S, const double tot[6]
 }
 
 // ---------------------------------------------------------------- per-body totals
-// One block per body.  mode 0 (after the centroid kernel): enclosed volume V^n of membranes
-// with a volume penalty; mode 1 (after the probe kernel): hydrodynamic totals and the velocity
-// / pose update of rigid bodies.  Other bodies return at once.
-__global__ void __launch_bounds__(FOLD_THREADS) k_fold_bodies(Pools P, int mode) {
+// After the probe kernel, one block per body: hydrodynamic totals and the velocity / pose update of
+// rigid bodies; other bodies return at once.
+__global__ void __launch_bounds__(FOLD_THREADS) k_fold_bodies(Pools P) {
     const int b = blockIdx.x;
     const BodyDev& B = P.bodies[b];
-    if (B.nv == 0) return;   // an empty slot of a slotted batch
-    if (mode == 0 ? (B.rigid || B.kv == 0.0) : !B.rigid) return;
-    double tot[FOLD_MAX];
-    if (mode == 0) fold_partials<1>(P, B, B.nblk_c, tot);
-    else fold_partials<6>(P, B, B.nblk_t, tot);
+    if (B.nv == 0 || !B.rigid) return;   // nv: an empty slot of a slotted batch
+    double tot[6];
+    fold_partials<6, FOLD_THREADS>(P, B, B.nblk_t, tot);
     if (threadIdx.x != 0) return;
-    if (mode == 0) { P.bstate[b].V = tot[0]; return; }
     // the state and the body constants are read into registers at once and stored once
     const BodyDev Bc = B;
     BodyState S = P.bstate[b];
@@ -1052,8 +963,8 @@ void launch_centroids(const Pools& P, int nblk_tri, int nblk_edge, bool wide, hi
         if (wide) hipLaunchKernelGGL((k_centroids<false, true>), dim3(nblk_tri), block, 0, s, P, nblk_tri);
     }
 }
-void launch_fold_bodies(const Pools& P, int nbodies, int mode, hipStream_t s) {
-    if (nbodies > 0) hipLaunchKernelGGL(k_fold_bodies, dim3(nbodies), dim3(FOLD_THREADS), 0, s, P, mode);
+void launch_fold_bodies(const Pools& P, int nbodies, hipStream_t s) {
+    if (nbodies > 0) hipLaunchKernelGGL(k_fold_bodies, dim3(nbodies), dim3(FOLD_THREADS), 0, s, P);
 }
 
 void launch_triangles(const Pools& P, int nblk_tri, int nblk_vel, bool wide, hipStream_t s) {

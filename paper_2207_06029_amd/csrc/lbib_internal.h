@@ -251,8 +251,9 @@ constexpr long long XCD_CHUNK_MAX_BYTES = 192LL << 20;
 void launch_sweep(const Pools& P, int storage, bool collide, bool a_to_b, int ntiles,
                   SweepShape shape, int xcd_chunk, hipStream_t s, hipEvent_t ev0 = nullptr,
                   hipEvent_t ev1 = nullptr);
-// nblk_w: total window blocks (each body gets blocks in proportion to its window capacity)
-void launch_window_moments(const Pools& P, int storage, bool from_b, int nblk_w, hipStream_t s);
+// nblk_w: total window blocks (each body gets blocks in proportion to its window capacity);
+// nvol: bodies whose enclosed volume is folded from the centroid kernel's partials (0: none)
+void launch_window_moments(const Pools& P, int storage, bool from_b, int nblk_w, int nvol, hipStream_t s);
 // rho[n] then u*[3n] in double (the host layout of lbib_get_macros), written to out[4n]
 void launch_macros_f64(const Pools& P, int storage, bool from_b, int job, long long n, double* out,
                        hipStream_t s);
@@ -270,8 +271,8 @@ void launch_init_eq(const Pools& P, int storage, bool to_b, int job, long long n
 // wide: some body's MLS support needs all 27 nodes around a point.
 void launch_centroids(const Pools& P, int nblk_tri, int nblk_edge, bool wide, hipStream_t s);
 void launch_triangles(const Pools& P, int nblk_tri, int nblk_vel, bool wide, hipStream_t s);
-// mode 0: volumes of membranes with a volume penalty; mode 1: rigid totals and pose update
-void launch_fold_bodies(const Pools& P, int nbodies, int mode, hipStream_t s);
+// rigid totals and pose update
+void launch_fold_bodies(const Pools& P, int nbodies, hipStream_t s);
 void launch_vertices(const Pools& P, int nblocks, hipStream_t s);
 void launch_body_totals(const Pools& P, int body, double* out6, hipStream_t s);
 

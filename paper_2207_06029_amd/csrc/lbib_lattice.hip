@@ -6,7 +6,7 @@
 // obtained by pulling g_i from x - e_i, with periodic wrap, halfway bounce-back from the
 // node's own opposite population, or the Zou-He closure on wet wall nodes.  Every reader
 // (sweep, moments, getters) uses the same pull, so the post-streaming state is never stored.
-#include "lbib_internal.h"
+#include "lbib_reduce.h"
 
 #include <hip/hip_ext.h>
 
@@ -776,8 +776,13 @@ void launch_sweep(const Pools& P, int storage, bool collide, bool a_to_b, int nt
 // A lone body's launch is one chain of dependent reads (arguments, job and layout, populations) with
 // about a node per thread: the job record is copied before the first store, which the compiler must
 // otherwise assume to change it, so all of it arrives in one round of scalar loads.
-template <typename S, bool SOLO>
-__global__ void __launch_bounds__(256) k_window_moments(Pools P, int from_b) {
+// VOL: blocks from nwin on fold the volumes of membranes with a volume penalty, one body each.
+// Nothing before the probes needs them, and a launch of their own cost a capsule in 75^3 4.2 us of a
+// 37 us step (now 33.5).  Without VOL the kernel keeps its registers: 64 jobs 639 us per step, 650 with
+// the unused branch.
+template <typename S, bool SOLO, bool VOL>
+__global__ void __launch_bounds__(256) k_window_moments(Pools P, int nwin, int from_b) {
+    if (VOL && (int)blockIdx.x >= nwin) { fold_volume<256>(P, blockIdx.x - nwin); return; }
     // blocks of a body are proportional to its window at rest; they stride over the current one
     const int b = block_body<SOLO>(P, P.blk_body_w, blockIdx.x);
     const BodyDev& B = body_of<SOLO>(P, b);
@@ -832,20 +837,23 @@ __global__ void __launch_bounds__(256) k_window_moments(Pools P, int from_b) {
     if (lb == 0 && threadIdx.x == 0) P.mdesc[b] = P.fdesc[b];
 }
 
-void launch_window_moments(const Pools& P, int storage, bool from_b, int nblk_w, hipStream_t s) {
-    if (nblk_w <= 0) return;
-    dim3 grid(nblk_w), block(256);
+template <typename S>
+static void window_moments_t(const Pools& P, bool from_b, int nblk_w, int nvol, hipStream_t s) {
+    const dim3 grid(nblk_w + nvol), block(256);
     const bool solo = P.solo_job >= 0;
-    if (storage == 0) {
-        if (solo) hipLaunchKernelGGL((k_window_moments<float, true>), grid, block, 0, s, P, (int)from_b);
-        else hipLaunchKernelGGL((k_window_moments<float, false>), grid, block, 0, s, P, (int)from_b);
-    } else if (storage == 1) {
-        if (solo) hipLaunchKernelGGL((k_window_moments<__half, true>), grid, block, 0, s, P, (int)from_b);
-        else hipLaunchKernelGGL((k_window_moments<__half, false>), grid, block, 0, s, P, (int)from_b);
+    if (nvol > 0) {
+        if (solo) hipLaunchKernelGGL((k_window_moments<S, true, true>), grid, block, 0, s, P, nblk_w, (int)from_b);
+        else hipLaunchKernelGGL((k_window_moments<S, false, true>), grid, block, 0, s, P, nblk_w, (int)from_b);
     } else {
-        if (solo) hipLaunchKernelGGL((k_window_moments<__hip_bfloat16, true>), grid, block, 0, s, P, (int)from_b);
-        else hipLaunchKernelGGL((k_window_moments<__hip_bfloat16, false>), grid, block, 0, s, P, (int)from_b);
+        if (solo) hipLaunchKernelGGL((k_window_moments<S, true, false>), grid, block, 0, s, P, nblk_w, (int)from_b);
+        else hipLaunchKernelGGL((k_window_moments<S, false, false>), grid, block, 0, s, P, nblk_w, (int)from_b);
     }
+}
+void launch_window_moments(const Pools& P, int storage, bool from_b, int nblk_w, int nvol, hipStream_t s) {
+    if (nblk_w <= 0) return;
+    if (storage == 0) window_moments_t<float>(P, from_b, nblk_w, nvol, s);
+    else if (storage == 1) window_moments_t<__half>(P, from_b, nblk_w, nvol, s);
+    else window_moments_t<__hip_bfloat16>(P, from_b, nblk_w, nvol, s);
 }
 
 // ---------------------------------------------------------------- getters / setters

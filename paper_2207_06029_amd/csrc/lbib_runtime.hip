@@ -818,7 +818,7 @@ lbib_status Batch::get_populations(int job, double* f) {
 
 // ---------------------------------------------------------------- stepping
 lbib_status Batch::prime() {
-    launch_window_moments(P, storage, cur_b, nblk_w, stream);
+    launch_window_moments(P, storage, cur_b, nblk_w, 0, stream);
     HIP_TRY(hipGetLastError());
     primed = true;
     return LBIB_OK;
@@ -826,10 +826,7 @@ lbib_status Batch::prime() {
 
 lbib_status Batch::enqueue_step(bool collide) {
     const bool bodies = collide && nbodies > 0;
-    if (bodies) {
-        launch_centroids(P, nblk_c, nblk_e, any_wide, stream);
-        if (any_volume) launch_fold_bodies(P, nbodies, 0, stream);
-    }
+    if (bodies) launch_centroids(P, nblk_c, nblk_e, any_wide, stream);
     if (timing && sweep_seq++ % timing_period == 0) {
         hipEvent_t a, b;
         lbib_status st = next_event(&a);
@@ -842,9 +839,9 @@ lbib_status Batch::enqueue_step(bool collide) {
     }
     cur_b = !cur_b;
     if (bodies) {
-        launch_window_moments(P, storage, cur_b, nblk_w, stream);
+        launch_window_moments(P, storage, cur_b, nblk_w, any_volume ? nbodies : 0, stream);
         launch_triangles(P, nblk_t, nblk_u, any_wide, stream);
-        if (any_rigid) launch_fold_bodies(P, nbodies, 1, stream);
+        if (any_rigid) launch_fold_bodies(P, nbodies, stream);
         launch_vertices(P, nblk_v, stream);
     }
     HIP_TRY(hipGetLastError());
@@ -1309,7 +1306,7 @@ lbib_status Batch::slot_admit(int s, const lbib_lattice_desc& d, const HostBody*
     if (st) return st;
     // moment windows of the new body (resident bodies get theirs again, bitwise the same)
     if (hb) {
-        launch_window_moments(P, storage, cur_b, nblk_w, stream);
+        launch_window_moments(P, storage, cur_b, nblk_w, 0, stream);
         HIP_TRY(hipGetLastError());
     }
     return LBIB_OK;
