@@ -118,7 +118,7 @@ struct WinDesc {
 };
 
 // A window is usable when 0 <= o < n and 1 <= w <= min(n, cap) on every axis, and on walled
-// axes o + w <= n.  Kernels that walk a window check this first.
+// axes o + w <= n.  Every writer of a layout keeps to it; the moments kernel tests it too.
 __host__ __device__ inline bool win_valid(const WinDesc& d, const int dims[3], const int cap[3],
                                           const int bc[6]) {
     for (int a = 0; a < 3; ++a) {
