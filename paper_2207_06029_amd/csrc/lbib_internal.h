@@ -229,6 +229,8 @@ __device__ __forceinline__ const JobDev& body_job(const Pools& P, const BodyDev&
 // Have values of the kernel arguments and tables in scalar registers here.  The compiler otherwise
 // leaves uniform loads behind the branches before their uses: a dependent round trip beyond the
 // scalar cache each, and a short launch consists of little else.
+// Uniform values read after it come through the vector cache (it counts as a store), so it belongs
+// after the last of them, and not into kernels that keep reading their tables.
 template <typename... T>
 __device__ __forceinline__ void loaded(const T&... v) { (..., [](const auto& x) { asm volatile("" ::"s"(x)); }(v)); }
 
