@@ -150,6 +150,8 @@ lbib_status lbib_lattice_create(const lbib_lattice_desc* desc, void* hip_stream,
         std::unique_ptr<Batch> B(new Batch());
         st = B->create_lattices({*desc}, desc->storage, hip_stream, workspace, ws_bytes);
         if (st) return st;
+        // graphs are allocated by the runtime: not where the caller brings the memory
+        B->auto_graph = !workspace;
         lbib_lattice* L = new lbib_lattice();
         L->batch = B.release();
         L->job = 0;

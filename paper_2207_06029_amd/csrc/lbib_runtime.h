@@ -64,6 +64,14 @@ void incidence_lists(const HostBody& h, int wt, int wh, std::vector<int>& vtl, s
 // steps per captured graph (even: the population buffers swap once per step)
 constexpr int GRAPH_STEPS = 16;
 
+// A lone small lattice replays graphs by itself.  Eager launches cost the host 4-5 us each, 20-30 us
+// per step, which is as long as the device takes up to about 2^18 nodes (capsule in 32^3 24.7-29.7 us
+// per step eager and 23.3 replayed, depending on the host; settling sphere in 48x48x77 38.7 and 32.9;
+// 75x51x67 31.2-34.2 and 31.5; from 128x64x128 on no difference, or a loss: 96x96x384 82.4 and 85.0).
+// Capturing costs 0.6 ms, 2.8 ms the first time in a process, so a lattice first runs AUTO_GRAPH_AFTER steps eagerly.
+constexpr long long AUTO_GRAPH_MAX_NODES = 1LL << 18;
+constexpr int AUTO_GRAPH_AFTER = 512;
+
 // Capacity of one slot of a slotted batch: every job admitted to the slot must fit it.
 struct SlotCaps {
     long long nodes = 0;   // lattice nodes
@@ -103,6 +111,8 @@ struct Batch {
     int xcd_chunk = 0;        // effective XCD chunk of the current shape and footprint
     bool use_graph = false;
     bool graph_valid = false;
+    bool auto_graph = false;   // replay graphs without being asked once that pays (auto_replay)
+    int settled = 0;           // steps enqueued since the graph became invalid, up to AUTO_GRAPH_AFTER
     hipGraph_t graph = nullptr;
     hipGraphExec_t graph_exec = nullptr;
     hipStream_t capture_stream = nullptr;
@@ -139,6 +149,8 @@ struct Batch {
     lbib_status enqueue_step(bool collide);
     lbib_status step(int nsteps, bool collide);
     lbib_status capture_graph();
+    bool auto_replay(int nsteps);
+    void drop_graph() { graph_valid = false; settled = 0; }
     lbib_status kernel_time(int kernel, double* ms, int64_t* count);
     void clear_events();
     lbib_status body_state(int bi, double* xyz, double* vel);

@@ -481,7 +481,7 @@ lbib_status Batch::retile() {
     HIP_TRY(hipMemcpyAsync(d_jobs, jobs.data(), sizeof(JobDev) * jobs.size(), hipMemcpyHostToDevice, stream));
     HIP_TRY(hipMemcpyAsync(d_tiles, tiles.data(), sizeof(int4) * tiles.size(), hipMemcpyHostToDevice, stream));
     P.tiles = d_tiles;
-    graph_valid = false;
+    drop_graph();
     return LBIB_OK;
 }
 
@@ -674,7 +674,7 @@ lbib_status Batch::rebuild_bodies() {
     HIP_TRY(hipMemcpyAsync(d_jobs, jobs.data(), sizeof(JobDev) * jobs.size(), hipMemcpyHostToDevice, stream));
     for (auto& h : hbodies) h.has_state = false;
     primed = false;
-    graph_valid = false;
+    drop_graph();
     HIP_TRY(hipStreamSynchronize(stream));
     return LBIB_OK;
 }
@@ -854,7 +854,7 @@ lbib_status Batch::step(int nsteps, bool collide) {
     if (collide && nbodies > 0 && !primed)
         if ((st = prime())) return st;
     if (!collide) primed = false;
-    if (use_graph && collide && !timing) {
+    if (collide && !timing && (use_graph || auto_replay(nsteps))) {
         // a graph holds GRAPH_STEPS steps (an even count, so the buffer parity returns to the
         // start); each replay costs a launch gap of several microseconds, which the steps share
         int k = 0;
@@ -880,12 +880,40 @@ lbib_status Batch::step(int nsteps, bool collide) {
         if ((st = enqueue_step(collide))) return st;
         ++step_count;
     }
+    settled = std::min((long long)AUTO_GRAPH_AFTER, (long long)settled + nsteps);
     if (timing) {
         HIP_TRY(hipEventRecord(s1, stream));
         step_events.push_back({s0, s1});
         step_event_steps += nsteps;
     }
     return LBIB_OK;
+}
+
+// Whether these steps of a lone lattice are replayed: its graph is there, or it has run long enough
+// for one to pay.  Steps that the caller is capturing are launched into the caller's graph.
+bool Batch::auto_replay(int nsteps) {
+    if (!auto_graph || !P.one_lattice || nbodies == 0 || jobs[0].n > AUTO_GRAPH_MAX_NODES) return false;
+    if (settled < AUTO_GRAPH_AFTER || nsteps - (cur_b ? 1 : 0) < GRAPH_STEPS) return false;
+    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(stream, &cs) != hipSuccess) {
+        (void)hipGetLastError();   // not to be taken for an error of the launches
+        return false;
+    }
+    if (cs != hipStreamCaptureStatusNone) return false;
+    if (graph_valid) return true;
+    // another thread may be capturing on its own streams: nothing here may end its capture
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    if (hipThreadExchangeStreamCaptureMode(&mode) != hipSuccess) { (void)hipGetLastError(); return false; }
+    const bool b = cur_b;
+    cur_b = false;   // the graph starts from buffer A; a step before it gets there (Batch::step)
+    const lbib_status st = capture_graph();
+    cur_b = b;
+    (void)hipThreadExchangeStreamCaptureMode(&mode);
+    if (st) {
+        (void)hipGetLastError();
+        auto_graph = false;   // eager, as before
+    }
+    return !st;
 }
 
 lbib_status Batch::capture_graph() {
