@@ -256,35 +256,6 @@ __device__ __forceinline__ double dot3(const double a[3], const double b[3]) {
     return a[0] * b[0] + a[1] * b[1] + a[2] * b[2];
 }
 
-// ---------------------------------------------------------------- window of a step
-// Force window = integer bounding box of the vertices plus WIN_MARGIN on each side, wrapped on
-// periodic axes, clipped on walled axes, never larger than the reserved capacity.
-__device__ __forceinline__ WinDesc window_from_box(const JobDev& J, const BodyDev& B, const int* bmin,
-                                                   const int* bmax, int& flag) {
-    WinDesc d;
-    const int dims[3] = {J.nx, J.ny, J.nz};
-    for (int a = 0; a < 3; ++a) {
-        int l = bmin[a] - WIN_MARGIN, h = bmax[a] + WIN_MARGIN;
-        if (h < l) { flag |= FLAG_NONFINITE; l = 0; h = 0; }
-        if (J.bc[2 * a] == 0) {
-            const int w = h - l + 1;
-            int o = l % dims[a];
-            if (o < 0) o += dims[a];
-            if (w >= dims[a]) { d.o[a] = 0; d.w[a] = dims[a]; d.b[a] = l - o; }
-            else { d.o[a] = o; d.w[a] = w; d.b[a] = l; }
-        } else {
-            if (l < 0) l = 0;
-            if (h > dims[a] - 1) h = dims[a] - 1;
-            d.o[a] = l < dims[a] ? l : dims[a] - 1;
-            d.w[a] = h >= l ? h - l + 1 : 1;
-            d.b[a] = d.o[a];
-        }
-        if (d.w[a] > B.win_cap[a]) { flag |= FLAG_WINDOW; d.w[a] = B.win_cap[a]; }
-        if (d.w[a] < 1) d.w[a] = 1;
-    }
-    return d;
-}
-
 // ---------------------------------------------------------------- hinge forces
 // Spring (Eq. strainFor) on the edge x1-x2 and bending -k_b sin(theta - theta0) dtheta/dx_r on
 // the four hinge vertices, theta the signed angle between the outward normals of (x1,x2,x3)
@@ -379,7 +350,7 @@ __device__ __forceinline__ void spread_block(const Pools& P, const JobDev& J, co
         bmin[a] = wave_minmax<false>(vb[a]);
         bmax[a] = wave_minmax<true>(vb[3 + a]);
     }
-    const WinDesc fd = window_from_box(J, B, bmin, bmax, err);
+    const WinDesc fd = window_from_box(J, B.win_cap, bmin, bmax, err);
     if (blk == 0 && threadIdx.x == 0) P.fdesc[b] = fd;
     const bool use_lds = w[0] <= 8 && w[1] <= 8 && w[2] <= SPREAD_LDS_Z;   // uniform over the block
     unsigned idx[N];
@@ -798,9 +769,6 @@ __global__ void __launch_bounds__(FOLD_THREADS) k_fold_bodies(Pools P) {
 }
 
 // ---------------------------------------------------------------- vertices
-__device__ __forceinline__ int box_lo(double v) { return (int)floor(fmin(fmax(v, -1e7), 1e7)); }
-__device__ __forceinline__ int box_hi(double v) { return (int)ceil(fmin(fmax(v, -1e7), 1e7)); }
-
 template <bool SOLO>
 __global__ void __launch_bounds__(VERT_BLOCK) k_vertices(Pools P) {
     const int b = block_body<SOLO>(P, P.blk_body_v, blockIdx.x);

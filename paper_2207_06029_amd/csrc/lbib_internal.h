@@ -118,7 +118,8 @@ struct WinDesc {
 };
 
 // A window is usable when 0 <= o < n and 1 <= w <= min(n, cap) on every axis, and on walled
-// axes o + w <= n.  Every writer of a layout keeps to it; the moments kernel tests it too.
+// axes o + w <= n.  The sweep reads the force window without testing this, so every layout comes from
+// window_from_box, which keeps to it for any box; the moments kernel tests it too.
 __host__ __device__ inline bool win_valid(const WinDesc& d, const int dims[3], const int cap[3],
                                           const int bc[6]) {
     for (int a = 0; a < 3; ++a) {
@@ -127,6 +128,39 @@ __host__ __device__ inline bool win_valid(const WinDesc& d, const int dims[3], c
         if (bc[2 * a] != 0 && d.o[a] + d.w[a] > dims[a]) return false;
     }
     return true;
+}
+
+// Integer bounds of a coordinate; positions beyond 1e7 are reported as a runaway state.
+__host__ __device__ inline int box_lo(double v) { return (int)floor(fmin(fmax(v, -1e7), 1e7)); }
+__host__ __device__ inline int box_hi(double v) { return (int)ceil(fmin(fmax(v, -1e7), 1e7)); }
+
+// Force window = integer bounding box of the vertices plus WIN_MARGIN on each side, wrapped on
+// periodic axes, clipped on walled axes, never larger than the reserved capacity.  A body past a wall
+// (a batch accepts it and reports its supports at the next synchronisation) gets the wall's plane.
+__host__ __device__ inline WinDesc window_from_box(const JobDev& J, const int cap[3], const int* bmin,
+                                                   const int* bmax, int& flag) {
+    WinDesc d;
+    const int dims[3] = {J.nx, J.ny, J.nz};
+    for (int a = 0; a < 3; ++a) {
+        int l = bmin[a] - WIN_MARGIN, h = bmax[a] + WIN_MARGIN;
+        if (h < l) { flag |= FLAG_NONFINITE; l = 0; h = 0; }
+        if (J.bc[2 * a] == 0) {
+            const int w = h - l + 1;
+            int o = l % dims[a];
+            if (o < 0) o += dims[a];
+            if (w >= dims[a]) { d.o[a] = 0; d.w[a] = dims[a]; d.b[a] = l - o; }
+            else { d.o[a] = o; d.w[a] = w; d.b[a] = l; }
+        } else {
+            if (l < 0) l = 0;
+            if (h > dims[a] - 1) h = dims[a] - 1;
+            d.o[a] = l < dims[a] ? l : dims[a] - 1;
+            d.w[a] = h >= l ? h - l + 1 : 1;
+            d.b[a] = d.o[a];
+        }
+        if (d.w[a] > cap[a]) { flag |= FLAG_WINDOW; d.w[a] = cap[a]; }
+        if (d.w[a] < 1) d.w[a] = 1;
+    }
+    return d;
 }
 
 struct BodyDev {

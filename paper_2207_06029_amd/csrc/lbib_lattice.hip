@@ -454,9 +454,9 @@ __device__ __forceinline__ void node_force(const Pools& P, const JobDev& J, int 
 
 // ---------------------------------------------------------------- fused sweep
 // Force window of a lattice's only body, read once per block, before the block's first store.  Every
-// writer of a layout keeps it inside the lattice and the body's capacity, so the sweep does not test
-// that again: the tests were a chain of scalar loads and branches at the start of every block (64-job
-// FP16 batch 633 -> 619 us per step, 12 jobs 81.7 -> 80.0).
+// layout, the host's too, comes from window_from_box, which keeps it inside the lattice and the body's
+// capacity, so the sweep does not test that again: the tests were a chain of scalar loads and branches
+// at the start of every block (64-job FP16 batch 633 -> 619 us per step, 12 jobs 81.7 -> 80.0).
 struct Win1 {
     int o[3], w[3];
     long long capn;

@@ -345,28 +345,12 @@ lbib_status build_body(const lbib_body_desc& d, const double* xyz, int nv, const
     return LBIB_OK;
 }
 
-// Window descriptor from a bounding box (same rule as the device code).
-static WinDesc window_for(const JobDev& J, const double lo[3], const double hi[3], const int cap[3], bool* over) {
-    WinDesc d;
-    const int dims[3] = {J.nx, J.ny, J.nz};
-    *over = false;
-    for (int a = 0; a < 3; ++a) {
-        int l = (int)std::floor(lo[a]) - WIN_MARGIN, h = (int)std::ceil(hi[a]) + WIN_MARGIN;
-        if (J.bc[2 * a] == 0) {
-            const int w = h - l + 1;
-            int o = l % dims[a];
-            if (o < 0) o += dims[a];
-            if (w >= dims[a]) { d.o[a] = 0; d.w[a] = dims[a]; d.b[a] = l - o; }
-            else { d.o[a] = o; d.w[a] = w; d.b[a] = l; }
-        } else {
-            l = std::max(l, 0);
-            h = std::min(h, dims[a] - 1);
-            d.o[a] = d.b[a] = l;
-            d.w[a] = h >= l ? h - l + 1 : 1;
-        }
-        if (d.w[a] > cap[a]) { *over = true; d.w[a] = cap[a]; }
-    }
-    return d;
+// Integer box of a body's vertices.
+static void vertex_box(const HostBody& h, int lo[3], int hi[3]) {
+    double l[3] = {1e300, 1e300, 1e300}, u[3] = {-1e300, -1e300, -1e300};
+    for (int v = 0; v < h.nv; ++v)
+        for (int a = 0; a < 3; ++a) { l[a] = std::min(l[a], h.x[3 * v + a]); u[a] = std::max(u[a], h.x[3 * v + a]); }
+    for (int a = 0; a < 3; ++a) { lo[a] = box_lo(l[a]); hi[a] = box_hi(u[a]); }
 }
 
 // Supports and probes of a body at positions x must stay off wall nodes.
@@ -595,9 +579,8 @@ lbib_status Batch::rebuild_bodies() {
         // state
         BodyState& S = bs[i];
         std::memset(&S, 0, sizeof S);
-        double lo[3] = {1e300, 1e300, 1e300}, hi[3] = {-1e300, -1e300, -1e300};
-        for (int v = 0; v < h.nv; ++v)
-            for (int a = 0; a < 3; ++a) { lo[a] = std::min(lo[a], h.x[3 * v + a]); hi[a] = std::max(hi[a], h.x[3 * v + a]); }
+        int lo[3], hi[3];
+        vertex_box(h, lo, hi);
         if (h.has_state) S = h.state;
         else {
             S.V = h.V0;
@@ -606,12 +589,12 @@ lbib_status Batch::rebuild_bodies() {
         }
         // every vertex block starts with the box of the current positions
         for (int k = 0; k < nbv; ++k) {
-            for (int a = 0; a < 3; ++a) vbox.push_back((int)std::floor(lo[a]));
-            for (int a = 0; a < 3; ++a) vbox.push_back((int)std::ceil(hi[a]));
+            vbox.insert(vbox.end(), lo, lo + 3);
+            vbox.insert(vbox.end(), hi, hi + 3);
         }
-        bool over = false;
-        fd[i] = h.has_state ? h.fdesc : window_for(J, lo, hi, B.win_cap, &over);
-        if (over) return fail(LBIB_EDOMAIN, "body does not fit its window");
+        int flag = 0;
+        fd[i] = h.has_state ? h.fdesc : window_from_box(J, B.win_cap, lo, hi, flag);
+        if (flag) return fail(LBIB_EDOMAIN, "body does not fit its window");
     }
     nbodies = (int)hbodies.size();
     P.solo_job = nbodies == 1 ? hbodies[0].job : -1;
@@ -1282,17 +1265,16 @@ lbib_status Batch::slot_admit(int s, const lbib_lattice_desc& d, const HostBody*
         std::vector<int> vtl, vhl;
         incidence_lists(h, B.vt_w, B.vh_w, vtl, vhl);
         std::vector<int> vb;
-        double lo[3] = {1e300, 1e300, 1e300}, hi[3] = {-1e300, -1e300, -1e300};
-        for (int v = 0; v < h.nv; ++v)
-            for (int a = 0; a < 3; ++a) { lo[a] = std::min(lo[a], h.x[3 * v + a]); hi[a] = std::max(hi[a], h.x[3 * v + a]); }
+        int lo[3], hi[3];
+        vertex_box(h, lo, hi);
         const int nbv = (h.nv + VERT_PER_BLOCK - 1) / VERT_PER_BLOCK;
         for (int k = 0; k < nbv; ++k) {
-            for (int a = 0; a < 3; ++a) vb.push_back((int)std::floor(lo[a]));
-            for (int a = 0; a < 3; ++a) vb.push_back((int)std::ceil(hi[a]));
+            vb.insert(vb.end(), lo, lo + 3);
+            vb.insert(vb.end(), hi, hi + 3);
         }
-        bool over = false;
-        const WinDesc fd = window_for(J, lo, hi, B.win_cap, &over);
-        if (over) return fail(LBIB_EDOMAIN, "body does not fit its window");
+        int flag = 0;
+        const WinDesc fd = window_from_box(J, B.win_cap, lo, hi, flag);
+        if (flag) return fail(LBIB_EDOMAIN, "body does not fit its window");
         BodyState S;
         std::memset(&S, 0, sizeof S);
         S.V = h.V0;

@@ -1,0 +1,79 @@
+"""The library's host code on the CPU, under a stand-in for the HIP runtime (hip_stub.hip) that runs no
+kernel and logs what is asked of it: the tables that the launches get."""
+import os
+import subprocess
+import sys
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+# In a process of its own: the stand-in is loaded first and globally, so the library's calls go to it.
+# torch stays out (it brings the real runtime).
+PREAMBLE = """
+import ctypes, sys
+sys.modules["torch"] = None
+sys.path.insert(0, {root!r})
+stub = ctypes.CDLL({stub!r}, mode=ctypes.RTLD_GLOBAL)
+stub.stub_log.restype = ctypes.c_char_p
+import numpy as np
+from paper_2207_06029_amd import api, inputs as I
+
+def log():
+    lines = stub.stub_log().decode().splitlines()
+    stub.stub_clear()
+    return lines
+"""
+
+
+@pytest.fixture(scope="module")
+def stub(tmp_path_factory):
+    from paper_2207_06029_amd import build as B
+    so = str(tmp_path_factory.mktemp("stub") / "libhip_stub.so")
+    r = subprocess.run([B.HIPCC, "--offload-host-only", "-O1", "-std=c++17", "-shared", "-fPIC", "-w", "-I", B.CSRC,
+                        os.path.join(ROOT, "tests", "hip_stub.hip"), "-o", so], capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr
+    return so
+
+
+def _run(stub, code):
+    r = subprocess.run([sys.executable, "-c", PREAMBLE.format(root=ROOT, stub=stub) + code], capture_output=True, text=True,
+                       timeout=300)
+    assert r.returncode == 0, r.stdout[-2000:] + r.stderr[-4000:]
+
+
+WINDOWS = """
+# a body beside, across and beyond either wall of axis a, and anywhere along a periodic axis; the tuner
+# sweeps with the layouts that the host wrote
+n = 48
+for a in range(3):
+    for at in (-1e12, -60.0, -9.0, -1.5, 0.0, 5.0, 23.5, 47.0, 48.5, 57.0, 64.0, 114.0, 1e9, 1e12):
+        for bc in (I.BC_PERIODIC, I.BC_ZOUHE_VELOCITY, I.BC_BOUNCEBACK):
+            for rigid in (0, 1):
+                kind = [I.BC_PERIODIC] * 6
+                kind[2 * a] = kind[2 * a + 1] = bc
+                spec = I.LatticeSpec(n, n, n, 0.8, bc=tuple(kind))
+                body = I.BodySpec(rigid=rigid, ks0=0.0 if rigid else 0.01, kb=0.0, kv=0.0, mass_ratio=2.0)
+                centre = [23.5] * 3
+                centre[a] = at
+                # far away no mesh keeps its shape in double: only the coordinates' range matters there
+                xyz, tri = I.spheroid_mesh(1, (4.0, 4.0, 4.0), (23.5,) * 3)
+                xyz[:, a] += at - 23.5
+                try:
+                    b = api.Batch([I.Job("wall", spec, body, xyz, tri, 1)], autotune=True)
+                except Exception as e:
+                    assert abs(at) >= 1e9 and "outward" in str(e), (a, at, bc, rigid, e)
+                    log()
+                    continue
+                b.step(1)
+                lines = log()
+                assert any("k_sweep" in l for l in lines)
+                assert not any(l.startswith("bad window") for l in lines), (a, at, bc, rigid)
+                b.destroy()
+"""
+
+
+def test_windows_of_bodies_past_a_wall_stay_in_the_lattice(stub):
+    """Batches take any body (a support on a wall is reported at the next synchronisation), and the sweep
+    reads the force window without testing its layout."""
+    _run(stub, WINDOWS)
