@@ -198,8 +198,10 @@ __device__ __forceinline__ double point_dot(const MlsLane<WIDE>& m, const double
 // inside the window and the fluid, every point of an ordinary step, take the first form (one vote
 // per wave): no wrap, no test per node, and the inactive slots hold valid indices too, so the
 // caller loads all of them without a branch.  The second form wraps periodic axes, reports support
-// nodes beyond a wall or the window, and gives their slots index 0.
-template <bool WIDE>
+// nodes beyond a wall or the window, and gives their slots index 0.  They stay in the point's moment
+// system, which would be singular without them and end the job as unstable, not as out of its domain;
+// DROP takes them out afterwards, for the spreading.
+template <bool WIDE, bool DROP = false>
 __device__ __forceinline__ void mls_index(const JobDev& J, const WinDesc& d, MlsLane<WIDE>& m,
                                           unsigned idx[MlsLane<WIDE>::N], int& err) {
     const int n[3] = {J.nx, J.ny, J.nz};
@@ -238,10 +240,8 @@ __device__ __forceinline__ void mls_index(const JobDev& J, const WinDesc& d, Mls
             i += (unsigned)t * st;
             st *= (unsigned)d.w[a];
         }
-        if (!ok) {
-            if (m.active[s]) err |= FLAG_WINDOW;
-            m.active[s] = false;
-        }
+        if (!ok && m.active[s]) err |= FLAG_WINDOW;
+        if (DROP && !ok) m.active[s] = false;
         idx[s] = ok ? i : 0u;
     }
 }
@@ -355,7 +355,7 @@ __device__ __forceinline__ void spread_block(const Pools& P, const JobDev& J, co
     const bool use_lds = w[0] <= 8 && w[1] <= 8 && w[2] <= SPREAD_LDS_Z;   // uniform over the block
     unsigned idx[N];
     if (!use_lds) {
-        mls_index<WIDE>(J, fd, m, idx, err);
+        mls_index<WIDE, true>(J, fd, m, idx, err);
         MLS_SLOTS(s, m)
             if (live && m.active[s])
                 for (int c = 0; c < 3; ++c)
