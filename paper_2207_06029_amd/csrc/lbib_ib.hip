@@ -137,7 +137,7 @@ __device__ __forceinline__ double rcp64(double x) {
 // p = (1, d), W = exp(-(|d| / (r_w alpha))^2) (Eqs. l2norm, intKernel).  The weights are
 // evaluated in FP32; the moment matrix is accumulated and factorised (A = L D L^T, unit L) in
 // FP64 on every lane.
-template <bool WIDE, bool FUSE = true>
+template <bool WIDE>
 __device__ __forceinline__ void mls_solve(MlsLane<WIDE>& m, float wq, bool want_grad, int& err) {
     double W[MlsLane<WIDE>::N];
     double A[10] = {};   // 00 01 02 03 11 12 13 22 23 33
@@ -167,11 +167,12 @@ __device__ __forceinline__ void mls_solve(MlsLane<WIDE>& m, float wq, bool want_
     const double i3 = rcp64(e3);
     if (!(e0 > 0.0 && e1 > 0.0 && e2 > 0.0 && e3 > 0.0)) err |= FLAG_NONFINITE;
     MLS_SLOTS(s, m) {
-        // v = A^{-1} p_k: L y = p, z = D^{-1} y, L^T v = z.  FUSE: the first column of L, a0j / e0,
-        // enters the differences as the unrounded product
-        const double y1 = FUSE ? fma(-i0, a01, m.d0[s]) : m.d0[s] - l10;
-        const double y2 = fma(-l21, y1, FUSE ? fma(-i0, a02, m.d1[s]) : m.d1[s] - l20);
-        const double y3 = fma(-l32, y2, fma(-l31, y1, FUSE ? fma(-i0, a03, m.d2[s]) : m.d2[s] - l30));
+        // v = A^{-1} p_k: L y = p, z = D^{-1} y, L^T v = z.  The first column of L, a0j / e0, enters
+        // the differences as the unrounded product; every fusion is written out, so that a body alone
+        // and in a batch (two instantiations) rounds alike
+        const double y1 = fma(-i0, a01, m.d0[s]);
+        const double y2 = fma(-l21, y1, fma(-i0, a02, m.d1[s]));
+        const double y3 = fma(-l32, y2, fma(-l31, y1, fma(-i0, a03, m.d2[s])));
         const double v3 = y3 * i3;
         const double v2 = fma(y2, i2, -(l32 * v3));
         const double v1 = fma(-l31, v3, fma(y1, i1, -(l21 * v2)));
@@ -494,7 +495,7 @@ __global__ void __launch_bounds__(IB_BLOCK, SOLO ? 1 : 4) k_centroids(Pools P, i
         cross3(pb, pc, bc);
         Vt = dot3(pa, bc) * (1.0 / 6.0);
     }
-    mls_solve<WIDE, SOLO>(m, B.wq, false, err);
+    mls_solve<WIDE>(m, B.wq, false, err);
     if (!SOLO) MLS_SLOTS(s, m) mom[s] = P.mwin[B.win_off + idx[s]];
     double U[3];
     for (int a = 0; a < 3; ++a) U[a] = point_dot<WIDE>(m, m.phi, 1, mom, 1 + a);
