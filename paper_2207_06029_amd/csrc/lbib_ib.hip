@@ -535,7 +535,8 @@ __global__ void __launch_bounds__(IB_BLOCK, SOLO ? 1 : 4) k_centroids(Pools P, i
             for (int a = 0; a < 3; ++a) { vb[a] = min(vb[a], e[i][a]); vb[3 + a] = max(vb[3 + a], e[i][3 + a]); }
     }
     spread_block<WIDE>(P, J, B, b, blk, vb, live, m, fx, err);
-    if (err && live) atomicOr(P.flags + B.job, err);
+    // spare groups report too: they repeat the last triangle, and their lanes take columns of the box
+    if (err) atomicOr(P.flags + B.job, err);
     if (B.rigid || B.kv == 0.0) return;
     // one partial of the volume per VOL_GROUP triangles, folded into V by the moments launch
     __shared__ double vol[PTS];
