@@ -150,7 +150,7 @@ struct Batch {
     lbib_status step(int nsteps, bool collide);
     lbib_status capture_graph();
     bool auto_replay(int nsteps);
-    void drop_graph() { graph_valid = false; settled = 0; }
+    lbib_status drop_graph();
     lbib_status kernel_time(int kernel, double* ms, int64_t* count);
     void clear_events();
     lbib_status body_state(int bi, double* xyz, double* vel);

@@ -465,8 +465,7 @@ lbib_status Batch::retile() {
     HIP_TRY(hipMemcpyAsync(d_jobs, jobs.data(), sizeof(JobDev) * jobs.size(), hipMemcpyHostToDevice, stream));
     HIP_TRY(hipMemcpyAsync(d_tiles, tiles.data(), sizeof(int4) * tiles.size(), hipMemcpyHostToDevice, stream));
     P.tiles = d_tiles;
-    drop_graph();
-    return LBIB_OK;
+    return drop_graph();
 }
 
 lbib_status Batch::set_shape(SweepShape s) {
@@ -518,6 +517,7 @@ lbib_status Batch::rebuild_bodies() {
     lbib_status st;
     if ((st = download_body_state())) return st;
     HIP_TRY(hipStreamSynchronize(stream));
+    if ((st = drop_graph())) return st;
     arena.release_from(mark_used, mark_owned);
     // order bodies by job
     std::stable_sort(hbodies.begin(), hbodies.end(), [](const HostBody& a, const HostBody& b) { return a.job < b.job; });
@@ -657,7 +657,6 @@ lbib_status Batch::rebuild_bodies() {
     HIP_TRY(hipMemcpyAsync(d_jobs, jobs.data(), sizeof(JobDev) * jobs.size(), hipMemcpyHostToDevice, stream));
     for (auto& h : hbodies) h.has_state = false;
     primed = false;
-    drop_graph();
     HIP_TRY(hipStreamSynchronize(stream));
     return LBIB_OK;
 }
@@ -899,12 +898,25 @@ bool Batch::auto_replay(int nsteps) {
     return !st;
 }
 
-lbib_status Batch::capture_graph() {
-    if (graph_exec) { HIP_TRY(hipGraphExecDestroy(graph_exec)); graph_exec = nullptr; }
+// Give up the captured steps: their tables or launch shape are about to change.
+lbib_status Batch::drop_graph() {
+    graph_valid = false;
+    settled = 0;
+    if (graph_exec) {
+        HIP_TRY(hipStreamSynchronize(stream));   // a replay may still run
+        HIP_TRY(hipGraphExecDestroy(graph_exec));
+        graph_exec = nullptr;
+    }
     if (graph) { HIP_TRY(hipGraphDestroy(graph)); graph = nullptr; }
+    return LBIB_OK;
+}
+
+// Capture GRAPH_STEPS steps.  Nothing is waited for: the caller's stream may be busy, and is ordered
+// by the replays that it gets.
+lbib_status Batch::capture_graph() {
+    if (graph) { HIP_TRY(hipGraphDestroy(graph)); graph = nullptr; }   // of a failed instantiation
     if (!capture_stream) HIP_TRY(hipStreamCreateWithFlags(&capture_stream, hipStreamNonBlocking));
     hipStream_t user = stream;
-    HIP_TRY(hipStreamSynchronize(user));
     HIP_TRY(hipStreamBeginCapture(capture_stream, hipStreamCaptureModeThreadLocal));
     // launches of the steps go to the capture stream; the caller's stream is restored below
     stream = capture_stream;

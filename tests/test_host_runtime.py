@@ -1,5 +1,5 @@
 """The library's host code on the CPU, under a stand-in for the HIP runtime (hip_stub.hip) that runs no
-kernel and logs what is asked of it: the tables that the launches get."""
+kernel and logs what is asked of it: the tables that the launches get, and when steps are replayed."""
 import os
 import subprocess
 import sys
@@ -23,6 +23,19 @@ def log():
     lines = stub.stub_log().decode().splitlines()
     stub.stub_clear()
     return lines
+
+def lattice(n=24, stream=4711):
+    lat = api.Lattice(I.LatticeSpec(n, n, n, 0.8, **I.shear_walls(0.01)), stream=stream)
+    xyz, tri = I.spheroid_mesh(1, (3.5, 3.5, 2.8), ((n - 1) / 2,) * 3)
+    body = I.BodySpec(rigid=0, ks0=0.01, kb=0.0, kv=0.0, mass_ratio=2.0)
+    lat.add_body(body, xyz, tri)
+    log()
+    return lat, lambda: lat.add_body(body, xyz, tri)
+
+def steps(lines, stream=4711):
+    "Steps run by these calls, one by one and in replays of 16."
+    single = sum("k_sweep" in l and l.endswith(f" {{stream}}") for l in lines)
+    return single, 16 * lines.count(f"replay {{stream}}")
 """
 
 
@@ -77,3 +90,38 @@ def test_windows_of_bodies_past_a_wall_stay_in_the_lattice(stub):
     """Batches take any body (a support on a wall is reported at the next synchronisation), and the sweep
     reads the force window without testing its layout."""
     _run(stub, WINDOWS)
+
+
+def test_steps_are_replayed_without_a_wait(stub):
+    """Stepping is asynchronous: nothing is waited for where steps are captured and replayed."""
+    _run(stub, """
+lat, _ = lattice()
+lat.step(512)
+assert steps(log()) == (512, 0)
+# a replay starts on an even step: single steps up to it, and for what is left over
+for n, single, replayed in ((15, 15, 0), (64, 16, 48), (16, 16, 0), (35, 3, 32), (16, 0, 16)):
+    lat.step(n)
+    lines = log()
+    assert steps(lines) == (single, replayed), (n, steps(lines))
+    assert not any(l.startswith("sync") for l in lines)
+""")
+
+
+def test_a_change_of_the_bodies_ends_the_replays(stub):
+    """The graph of the old tables is given up once its replays have ended, and a new one is captured."""
+    _run(stub, """
+lat, again = lattice()
+lat.step(512)
+lat.step(64)
+assert steps(log()) == (512, 64)
+again()
+lines = log()
+assert lines.count("exec_destroy") == 1 and "exec_destroy busy" not in lines
+lat.step(511)
+lat.step(65)
+assert steps(log()) == (576, 0)
+lat.step(64)
+lines = log()
+assert steps(lines) == (0, 64) and sum(l.startswith("begin") for l in lines) == 1
+assert not any(l.startswith("sync") for l in lines)
+""")
