@@ -876,6 +876,10 @@ lbib_status Batch::step(int nsteps, bool collide) {
 bool Batch::auto_replay(int nsteps) {
     if (!auto_graph || !P.one_lattice || nbodies == 0 || jobs[0].n > AUTO_GRAPH_MAX_NODES) return false;
     if (settled < AUTO_GRAPH_AFTER || nsteps - (cur_b ? 1 : 0) < GRAPH_STEPS) return false;
+    // eager launches go to the stream's device; a graph belongs to the current one
+    int dev = -1;
+    if (hipGetDevice(&dev) != hipSuccess) { (void)hipGetLastError(); return false; }
+    if (dev != device) return false;
     hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
     if (hipStreamIsCapturing(stream, &cs) != hipSuccess) {
         (void)hipGetLastError();   // not to be taken for an error of the launches

@@ -125,3 +125,22 @@ lines = log()
 assert steps(lines) == (0, 64) and sum(l.startswith("begin") for l in lines) == 1
 assert not any(l.startswith("sync") for l in lines)
 """)
+
+
+def test_steps_under_another_device_are_not_replayed(stub):
+    """Launches go to their stream's device whichever is current; a graph would be captured for, and
+    launched on, the current one."""
+    _run(stub, """
+lat, _ = lattice()
+lat.step(512)
+stub.stub_set_device(1)
+lat.step(64)
+lines = log()
+assert steps(lines) == (576, 0) and not any(l.startswith("begin") for l in lines)
+stub.stub_set_device(0)
+lat.step(64)
+assert steps(log()) == (0, 64)
+stub.stub_set_device(1)
+lat.step(64)
+assert steps(log()) == (64, 0)
+""")
