@@ -975,7 +975,16 @@ void Batch::clear_events() {
 
 // Destruction cannot report errors: every release is attempted and its status dropped.
 Batch::~Batch() {
-    if (stream) (void)hipStreamSynchronize(stream);
+    if (stream) {
+        (void)hipStreamSynchronize(stream);
+    } else if (graph_exec) {
+        // replays run on the default stream of the batch's device
+        int cur = device;
+        (void)hipGetDevice(&cur);
+        if (cur != device) (void)hipSetDevice(device);
+        (void)hipStreamSynchronize(nullptr);
+        if (cur != device) (void)hipSetDevice(cur);
+    }
     clear_events();
     for (hipEvent_t e : event_pool) (void)hipEventDestroy(e);
     if (graph_exec) (void)hipGraphExecDestroy(graph_exec);

@@ -58,6 +58,7 @@ extern "C" {
 const char* stub_log() { return g_log.c_str(); }
 void stub_clear() { g_log.clear(); }
 void stub_set_device(int d) { g_device = d; }
+void stub_log_device() { say("device " + std::to_string(g_device)); }
 void stub_set_capturing(void* s, int on) { if (on) g_capturing.insert((hipStream_t)s); else g_capturing.erase((hipStream_t)s); }
 
 void** __hipRegisterFatBinary(const void*) { static void* h; return &h; }
@@ -93,7 +94,11 @@ hipError_t hipEventElapsedTime(float* ms, hipEvent_t, hipEvent_t) { *ms = 1.f; r
 
 hipError_t hipStreamCreateWithFlags(hipStream_t* s, unsigned) { *s = (hipStream_t)(size_t)++g_handle; return hipSuccess; }
 hipError_t hipStreamDestroy(hipStream_t) { return hipSuccess; }
-hipError_t hipStreamSynchronize(hipStream_t s) { say("sync " + name(s)); waited(); return hipSuccess; }
+hipError_t hipStreamSynchronize(hipStream_t s) {
+    say("sync " + name(s));
+    if (s || g_device == 0) waited();   // the default stream is the current device's; lattices live on device 0
+    return hipSuccess;
+}
 hipError_t hipStreamIsCapturing(hipStream_t s, hipStreamCaptureStatus* c) {
     *c = g_capturing.count(s) ? hipStreamCaptureStatusActive : hipStreamCaptureStatusNone;
     return hipSuccess;

@@ -144,3 +144,22 @@ stub.stub_set_device(1)
 lat.step(64)
 assert steps(log()) == (64, 0)
 """)
+
+
+def test_destroying_a_lattice_waits_for_its_replays(stub):
+    """On the default stream too, and for the lattice's device where another one is current."""
+    _run(stub, """
+for stream in (4711, None):
+    for current in (0, 1):
+        lat, _ = lattice(stream=stream)
+        lat.step(512)
+        lat.step(64)
+        assert steps(log(), stream or 0) == (512, 64)
+        stub.stub_set_device(current)
+        lat.destroy()
+        lines = log()
+        assert lines.count("exec_destroy") == 1 and "exec_destroy busy" not in lines
+        stub.stub_log_device()
+        assert log() == [f"device {current}"]
+        stub.stub_set_device(0)
+""")
