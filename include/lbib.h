@@ -157,8 +157,8 @@ lbib_status lbib_body_set_velocity(lbib_lattice* lat, int32_t body, const double
 /* Advance nsteps time steps (Sec. 1, one step = IB forcing, collide+stream, structure
  * update).  Asynchronous.  A lattice of up to 2^18 nodes with a body and no caller workspace
  * captures its steps once, after 512 of them and again after bodies were added, and replays
- * them from then on in calls of 16 steps or more: that call allocates (a graph, a stream) but
- * waits for nothing.  Steps that the caller captures are launched into the caller's graph. */
+ * them from then on in calls of 16 steps or more (within the first call if that is 512 steps
+ * longer): that call allocates (a graph, a stream) but waits for nothing.  Steps that the caller captures are launched into the caller's graph. */
 lbib_status lbib_step(lbib_lattice* lat, int32_t nsteps);
 
 /* Advance nsteps pure streaming steps (no collision, no bodies).  Asynchronous. */

@@ -68,7 +68,8 @@ constexpr int GRAPH_STEPS = 16;
 // per step, which is as long as the device takes up to about 2^18 nodes (capsule in 32^3 24.7-29.7 us
 // per step eager and 23.3 replayed, depending on the host; settling sphere in 48x48x77 38.7 and 32.9;
 // 75x51x67 31.2-34.2 and 31.5; from 128x64x128 on no difference, or a loss: 96x96x384 82.4 and 85.0).
-// Capturing costs 0.6 ms, 2.8 ms the first time in a process, so a lattice first runs AUTO_GRAPH_AFTER steps eagerly.
+// Capturing costs 0.6 ms, 2.8 ms the first time in a process, so a lattice first runs AUTO_GRAPH_AFTER
+// steps eagerly; the rest of the same call is replayed if it is at least as long, and later calls are.
 constexpr long long AUTO_GRAPH_MAX_NODES = 1LL << 18;
 constexpr int AUTO_GRAPH_AFTER = 512;
 
@@ -111,7 +112,7 @@ struct Batch {
     int xcd_chunk = 0;        // effective XCD chunk of the current shape and footprint
     bool use_graph = false;
     bool graph_valid = false;
-    bool auto_graph = false;   // replay graphs without being asked once that pays (auto_replay)
+    bool auto_graph = false;   // replay graphs without being asked once that pays (may_replay)
     int settled = 0;           // steps enqueued since the graph became invalid, up to AUTO_GRAPH_AFTER
     hipGraph_t graph = nullptr;
     hipGraphExec_t graph_exec = nullptr;
@@ -149,7 +150,8 @@ struct Batch {
     lbib_status enqueue_step(bool collide);
     lbib_status step(int nsteps, bool collide);
     lbib_status capture_graph();
-    bool auto_replay(int nsteps);
+    bool may_replay();
+    bool auto_capture();
     lbib_status drop_graph();
     lbib_status kernel_time(int kernel, double* ms, int64_t* count);
     void clear_events();

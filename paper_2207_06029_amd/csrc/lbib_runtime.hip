@@ -836,33 +836,45 @@ lbib_status Batch::step(int nsteps, bool collide) {
     if (collide && nbodies > 0 && !primed)
         if ((st = prime())) return st;
     if (!collide) primed = false;
-    if (collide && !timing && (use_graph || auto_replay(nsteps))) {
-        // a graph holds GRAPH_STEPS steps (an even count, so the buffer parity returns to the
-        // start); each replay costs a launch gap of several microseconds, which the steps share
-        int k = 0;
-        if (cur_b && nsteps > 0) { if ((st = enqueue_step(true))) return st; k = 1; ++step_count; }
-        const int reps = (nsteps - k) / GRAPH_STEPS;
-        if (reps > 0) {
-            if (!graph_valid) { if ((st = capture_graph())) return st; }
-            for (int p = 0; p < reps; ++p) HIP_TRY(hipGraphLaunch(graph_exec, stream));
-            step_count += (long long)GRAPH_STEPS * reps;
-        }
-        for (int r = k + reps * GRAPH_STEPS; r < nsteps; ++r) {
-            if ((st = enqueue_step(true))) return st;
-            ++step_count;
-        }
-        return LBIB_OK;
+    // steps launched one by one first, then replays of the captured steps, which start from buffer A
+    // (a graph holds GRAPH_STEPS steps, an even count, so the buffer parity returns to the start; each
+    // replay costs a launch gap of several microseconds, which the steps share), then what is left
+    int lead = nsteps, reps = 0;
+    if (collide && !timing && (use_graph || auto_graph)) {
+        const int first = use_graph ? 0 : AUTO_GRAPH_AFTER - settled;
+        lead = first + ((first + (cur_b ? 1 : 0)) & 1);
+        reps = nsteps > lead ? (nsteps - lead) / GRAPH_STEPS : 0;
+        // a call that still has steps to run before the capture needs enough after it to pay for it
+        if (first > 0 && reps * GRAPH_STEPS < AUTO_GRAPH_AFTER) reps = 0;
+        if (reps > 0 && !use_graph && !may_replay()) reps = 0;
+        if (reps == 0) lead = nsteps;
     }
     hipEvent_t s0 = nullptr, s1 = nullptr;
     if (timing) {
         if ((st = next_event(&s0)) || (st = next_event(&s1))) return st;
         HIP_TRY(hipEventRecord(s0, stream));
     }
-    for (int i = 0; i < nsteps; ++i) {
-        if ((st = enqueue_step(collide))) return st;
-        ++step_count;
+    const auto single = [&](int n) -> lbib_status {
+        for (int i = 0; i < n; ++i) {
+            if ((st = enqueue_step(collide))) return st;
+            ++step_count;
+        }
+        settled = (int)std::min<long long>(AUTO_GRAPH_AFTER, (long long)settled + n);
+        return LBIB_OK;
+    };
+    if ((st = single(lead))) return st;
+    if (reps > 0 && !graph_valid) {
+        if (use_graph) {
+            if ((st = capture_graph())) return st;
+        } else if (!auto_capture()) {
+            reps = 0;   // launched one by one below
+        }
     }
-    settled = std::min((long long)AUTO_GRAPH_AFTER, (long long)settled + nsteps);
+    for (int p = 0; p < reps; ++p) {
+        HIP_TRY(hipGraphLaunch(graph_exec, stream));
+        step_count += GRAPH_STEPS;
+    }
+    if ((st = single(nsteps - lead - reps * GRAPH_STEPS))) return st;
     if (timing) {
         HIP_TRY(hipEventRecord(s1, stream));
         step_events.push_back({s0, s1});
@@ -871,11 +883,10 @@ lbib_status Batch::step(int nsteps, bool collide) {
     return LBIB_OK;
 }
 
-// Whether these steps of a lone lattice are replayed: its graph is there, or it has run long enough
-// for one to pay.  Steps that the caller is capturing are launched into the caller's graph.
-bool Batch::auto_replay(int nsteps) {
-    if (!auto_graph || !P.one_lattice || nbodies == 0 || jobs[0].n > AUTO_GRAPH_MAX_NODES) return false;
-    if (settled < AUTO_GRAPH_AFTER || nsteps - (cur_b ? 1 : 0) < GRAPH_STEPS) return false;
+// Whether steps of a lone lattice may be replayed unasked.  Steps that the caller is capturing are
+// launched into the caller's graph.
+bool Batch::may_replay() {
+    if (!P.one_lattice || nbodies == 0 || jobs[0].n > AUTO_GRAPH_MAX_NODES) return false;
     // eager launches go to the stream's device; a graph belongs to the current one
     int dev = -1;
     if (hipGetDevice(&dev) != hipSuccess) { (void)hipGetLastError(); return false; }
@@ -885,19 +896,21 @@ bool Batch::auto_replay(int nsteps) {
         (void)hipGetLastError();   // not to be taken for an error of the launches
         return false;
     }
-    if (cs != hipStreamCaptureStatusNone) return false;
-    if (graph_valid) return true;
+    return cs == hipStreamCaptureStatusNone;
+}
+
+// Capture unasked; false: the steps are launched one by one, now and from then on.
+bool Batch::auto_capture() {
     // another thread may be capturing on its own streams: nothing here may end its capture
     hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
-    if (hipThreadExchangeStreamCaptureMode(&mode) != hipSuccess) { (void)hipGetLastError(); return false; }
-    const bool b = cur_b;
-    cur_b = false;   // the graph starts from buffer A; a step before it gets there (Batch::step)
-    const lbib_status st = capture_graph();
-    cur_b = b;
-    (void)hipThreadExchangeStreamCaptureMode(&mode);
+    lbib_status st = LBIB_EDEVICE;
+    if (hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess) {
+        st = capture_graph();
+        (void)hipThreadExchangeStreamCaptureMode(&mode);
+    }
     if (st) {
         (void)hipGetLastError();
-        auto_graph = false;   // eager, as before
+        auto_graph = false;
     }
     return !st;
 }

@@ -163,3 +163,18 @@ for stream in (4711, None):
         assert log() == [f"device {current}"]
         stub.stub_set_device(0)
 """)
+
+
+def test_a_long_first_call_is_replayed_after_its_first_steps(stub):
+    _run(stub, """
+# steps of calls on a new lattice: (single, replayed) of each
+for calls, want in ((((2048,), [(512, 1536)])), ((1024,), [(512, 512)]), ((1023, 17), [(1023, 0), (1, 16)]),
+                    ((3, 1100, 16), [(3, 0), (509 + 15, 576), (16, 0)]), ((511, 65, 64), [(511, 0), (65, 0), (0, 64)])):
+    lat, _ = lattice()
+    got = []
+    for n in calls:
+        lat.step(n)
+        got.append(steps(log()))
+    assert got == want, (calls, got)
+    assert lat.step_count == sum(calls)
+""")
