@@ -38,3 +38,32 @@ def test_a_long_first_call_equals_single_steps(api, storage):
     for _ in range(1103):
         b.step(1)
     _equal(a, b)
+
+
+def test_a_body_between_replayed_stretches(api):
+    (a, more_a), (b, more_b) = _lattice(api), _lattice(api)
+    for more, bodies in ((more_a, 1), (None, 2)):
+        a.step(512)
+        a.step(64)
+        for _ in range(576):
+            b.step(1)
+        _equal(a, b, bodies)
+        if more:
+            assert more_a() == more_b() == 1
+
+
+def test_a_replay_is_captured_while_the_stream_is_busy(api):
+    import torch
+    s = torch.cuda.Stream()
+    (a, _), (b, _) = _lattice(api, stream=s), _lattice(api)
+    a.step(512)
+    s.synchronize()
+    with torch.cuda.stream(s):
+        torch.cuda._sleep(2_000_000_000)   # about a second of the GPU's clock
+        slept = torch.cuda.Event()
+        slept.record()
+    a.step(64)
+    assert not slept.query()
+    for _ in range(576):
+        b.step(1)
+    _equal(a, b)
