@@ -272,11 +272,35 @@ __device__ __forceinline__ void loaded(const T&... v) { (..., [](const auto& x) 
 struct SweepShape {
     int block;          // threads per block
     int npt;            // nodes per thread (block-strided)
-    int xcd_chunk;      // > 0: XCD_CHUNK tiles per XCD and turn; 0: dispatch order; -1: chosen by footprint
+    int xcd_chunk;      // tiles an XCD takes per turn (0: dispatch order; -1: chosen by footprint)
 };
 // Chunked XCD order pays while the two population buffers stay in the Infinity Cache (256 MB);
 // beyond it, dispatch order keeps all XCDs streaming the same region.
 constexpr int XCD_CHUNK = 8;
+// Order in which blocks take the sweep's tiles.  The dispatcher deals consecutive blocks to the 8 XCDs in
+// turn, each with its own L2.  With chunk = C > 0 the first blocks, whole turns of 8 C, are remapped so
+// that every XCD takes C consecutive tiles per turn: the rows a tile pulls from its neighbours were
+// mostly just read through the same L2.  The rest keep their own tile (a bijection).  The turn of a block
+// is a product with the turn's reciprocal, rounded up to 32 bits: exact for all bid < 2^31, any chunk.
+struct SweepOrder {
+    unsigned limit, chunk, magic, shift;   // limit: blocks in whole turns (0: dispatch order)
+};
+inline SweepOrder sweep_order(unsigned T, int chunk) {
+    SweepOrder o = {0, 0, 0, 0};
+    if (chunk <= 0 || (unsigned)chunk > T / 8) return o;
+    const unsigned span = 8u * (unsigned)chunk;
+    o.limit = T / span * span;
+    o.chunk = (unsigned)chunk;
+    while ((2ULL << o.shift) < span) ++o.shift;   // 2^shift < span <= 2^(shift + 1)
+    o.magic = (unsigned)(((1ULL << (32 + o.shift)) + span - 1) / span);
+    return o;
+}
+__host__ __device__ inline unsigned sweep_tile(const SweepOrder& o, unsigned bid) {
+    const unsigned turn = (unsigned)(((unsigned long long)bid * o.magic) >> 32) >> o.shift;
+    const unsigned at = turn * 8 * o.chunk, tile = at + (bid & 7) * o.chunk + ((bid - at) >> 3);
+    // a mask in place of a choice: behind a branch the compiler would load the order only there
+    return bid + ((tile - bid) & (unsigned)((int)(bid - o.limit) >> 31));
+}
 // nodes of the smallest sweep tile (block size x nodes per thread) of any launch shape
 constexpr int MIN_TILE_NODES = 128;
 constexpr long long XCD_CHUNK_MAX_BYTES = 192LL << 20;

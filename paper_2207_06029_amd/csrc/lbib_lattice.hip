@@ -670,17 +670,8 @@ __device__ __forceinline__ void sweep_node(const Pools& P, const JobDev& J, cons
 // scheduled for eight waves (96x96x384 51.6 -> 49.1 us); FP32 lost 0.5 % by that, and the batched
 // 16-bit form spilled scalars (918 us).
 template <typename S, bool COLLIDE, int NPT, bool OFF32, bool ONE>
-__global__ void __launch_bounds__(1024, ONE && sizeof(S) == 2 ? 8 : 4) __attribute__((amdgpu_num_sgpr(96))) k_sweep(Pools P, int a_to_b, int xcd_chunk) {
-    // The dispatcher deals consecutive blocks to the 8 XCDs in turn, each with its own L2.
-    // With xcd_chunk set the blocks are remapped so that every XCD takes C = XCD_CHUNK consecutive
-    // tiles per turn: the rows a tile pulls from its neighbours were mostly just read through
-    // the same L2.  Blocks past the last whole turn keep their own tile (a bijection).
-    const unsigned T = gridDim.x, bid = blockIdx.x;
-    int tile = bid;
-    if (xcd_chunk > 0) {
-        constexpr int C = XCD_CHUNK, span = 8 * C;
-        if (bid < T / span * span) tile = bid / span * span + (bid & 7) * C + (bid >> 3) % C;
-    }
+__global__ void __launch_bounds__(1024, ONE && sizeof(S) == 2 ? 8 : 4) __attribute__((amdgpu_num_sgpr(96))) k_sweep(Pools P, int a_to_b, SweepOrder order) {
+    const int tile = (int)sweep_tile(order, blockIdx.x);
     const int4 te = P.tiles[tile];
     const int job = ONE ? 0 : te.x;
     const JobDev& J = P.jobs[job];
@@ -726,40 +717,40 @@ __global__ void __launch_bounds__(1024, ONE && sizeof(S) == 2 ? 8 : 4) __attribu
 }
 
 template <typename S, bool C, int NPT, bool OFF32, bool ONE = false>
-static void sweep_n(const Pools& P, bool a_to_b, int chunk, dim3 grid, dim3 block, hipStream_t s,
+static void sweep_n(const Pools& P, bool a_to_b, SweepOrder order, dim3 grid, dim3 block, hipStream_t s,
                     hipEvent_t ev0, hipEvent_t ev1) {
     if (ev0 || ev1)
-        hipExtLaunchKernelGGL((k_sweep<S, C, NPT, OFF32, ONE>), grid, block, 0, s, ev0, ev1, 0, P, (int)a_to_b, chunk);
+        hipExtLaunchKernelGGL((k_sweep<S, C, NPT, OFF32, ONE>), grid, block, 0, s, ev0, ev1, 0, P, (int)a_to_b, order);
     else
-        hipLaunchKernelGGL((k_sweep<S, C, NPT, OFF32, ONE>), grid, block, 0, s, P, (int)a_to_b, chunk);
+        hipLaunchKernelGGL((k_sweep<S, C, NPT, OFF32, ONE>), grid, block, 0, s, P, (int)a_to_b, order);
 }
 
 template <typename S, bool C, bool OFF32>
-static void sweep_o(const Pools& P, bool a_to_b, int ntiles, SweepShape sh, int chunk, hipStream_t s,
+static void sweep_o(const Pools& P, bool a_to_b, int ntiles, SweepShape sh, SweepOrder order, hipStream_t s,
                     hipEvent_t ev0, hipEvent_t ev1) {
     dim3 grid(ntiles), block(sh.block);
     switch (sh.npt) {
         case 1:
             // a single lattice keeps one node per thread; batches may autotune to any shape
-            if (P.one_lattice) sweep_n<S, C, 1, OFF32, true>(P, a_to_b, chunk, grid, block, s, ev0, ev1);
-            else sweep_n<S, C, 1, OFF32>(P, a_to_b, chunk, grid, block, s, ev0, ev1);
+            if (P.one_lattice) sweep_n<S, C, 1, OFF32, true>(P, a_to_b, order, grid, block, s, ev0, ev1);
+            else sweep_n<S, C, 1, OFF32>(P, a_to_b, order, grid, block, s, ev0, ev1);
             break;
-        case 2: sweep_n<S, C, 2, OFF32>(P, a_to_b, chunk, grid, block, s, ev0, ev1); break;
-        default: sweep_n<S, C, 4, OFF32>(P, a_to_b, chunk, grid, block, s, ev0, ev1); break;
+        case 2: sweep_n<S, C, 2, OFF32>(P, a_to_b, order, grid, block, s, ev0, ev1); break;
+        default: sweep_n<S, C, 4, OFF32>(P, a_to_b, order, grid, block, s, ev0, ev1); break;
     }
 }
 
 template <typename S, bool C>
-static void sweep_t(const Pools& P, bool a_to_b, int ntiles, SweepShape sh, int chunk, hipStream_t s,
+static void sweep_t(const Pools& P, bool a_to_b, int ntiles, SweepShape sh, SweepOrder order, hipStream_t s,
                     hipEvent_t ev0, hipEvent_t ev1) {
-    if (P.pop32) sweep_o<S, C, true>(P, a_to_b, ntiles, sh, chunk, s, ev0, ev1);
-    else sweep_o<S, C, false>(P, a_to_b, ntiles, sh, chunk, s, ev0, ev1);
+    if (P.pop32) sweep_o<S, C, true>(P, a_to_b, ntiles, sh, order, s, ev0, ev1);
+    else sweep_o<S, C, false>(P, a_to_b, ntiles, sh, order, s, ev0, ev1);
 }
 
 void launch_sweep(const Pools& P, int storage, bool collide, bool a_to_b, int ntiles,
                   SweepShape shape, int xcd_chunk, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1) {
     if (ntiles <= 0) return;
-    const int c = xcd_chunk;
+    const SweepOrder c = sweep_order((unsigned)ntiles, xcd_chunk);
     if (storage == 0) collide ? sweep_t<float, true>(P, a_to_b, ntiles, shape, c, s, ev0, ev1)
                               : sweep_t<float, false>(P, a_to_b, ntiles, shape, c, s, ev0, ev1);
     else if (storage == 1) collide ? sweep_t<__half, true>(P, a_to_b, ntiles, shape, c, s, ev0, ev1)

@@ -55,6 +55,7 @@ hipError_t launched(const void* f, dim3 grid, void** args, hipStream_t s) {
 
 extern "C" {
 
+unsigned stub_sweep_tile(unsigned T, unsigned bid, int chunk) { return lbib::sweep_tile(lbib::sweep_order(T, chunk), bid); }
 const char* stub_log() { return g_log.c_str(); }
 void stub_clear() { g_log.clear(); }
 void stub_set_device(int d) { g_device = d; }

@@ -178,3 +178,21 @@ for calls, want in ((((2048,), [(512, 1536)])), ((1024,), [(512, 512)]), ((1023,
     assert got == want, (calls, got)
     assert lat.step_count == sum(calls)
 """)
+
+
+def test_sweep_tiles_in_the_order_of_the_chunk(stub):
+    """Blocks go to XCD bid % 8: in every whole turn each takes its own run of `chunk` tiles in order, for
+    any chunk of a tuning line, and every tile is taken once."""
+    _run(stub, """
+for T in (1, 7, 24, 63, 64, 65, 128, 200, 1000):
+    for chunk in (0, 1, 2, 3, 5, 8, 13, 25, 125, 126, 1 << 29, 2**31 - 1):
+        order = [stub.stub_sweep_tile(T, bid, chunk) for bid in range(T)]
+        assert sorted(order) == list(range(T)), (T, chunk)
+        turns = T // (8 * chunk) if chunk else 0
+        for turn in range(turns):
+            for xcd in range(8):
+                at = 8 * chunk * turn
+                got = order[at + xcd:at + 8 * chunk:8]
+                assert got == list(range(at + xcd * chunk, at + (xcd + 1) * chunk)), (T, chunk)
+        assert order[8 * chunk * turns:] == list(range(8 * chunk * turns, T))
+""")
