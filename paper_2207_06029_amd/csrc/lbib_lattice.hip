@@ -475,7 +475,7 @@ __device__ __forceinline__ Win1 load_win1(const Pools& P, const JobDev& J) {
 }
 // The same for a batch of one lattice whose one body (index 0) comes with the kernel arguments:
 // the layout load does not wait for the job record.
-__device__ __forceinline__ Win1 load_win1_one(const Pools& P, const JobDev& J) {
+__device__ __forceinline__ Win1 load_win1_one(const Pools& P) {
     Win1 W;
     const WinDesc d = P.fdesc[0];
     const BodyDev& B = P.solo_body;
@@ -680,7 +680,7 @@ __global__ void __launch_bounds__(1024, ONE && sizeof(S) == 2 ? 8 : 4) __attribu
     const long long base = (long long)(tile - J.tile0) * blockDim.x * NPT;
     Win1 W = {};
     if (ONE) {
-        if (COLLIDE && P.solo_job >= 0) W = load_win1_one(P, J);
+        if (COLLIDE && P.solo_job >= 0) W = load_win1_one(P);
     } else if (COLLIDE && J.nbodies == 1) {
         W = load_win1(P, J);
     }
@@ -764,7 +764,9 @@ void launch_sweep(const Pools& P, int storage, bool collide, bool a_to_b, int nt
 // (rho - 1, u*) with u* = sum f e / rho, and clear the force window for the next step.
 // A lone body's launch is one chain of dependent reads (arguments, job and layout, populations) with
 // about a node per thread: the job record is copied before the first store, which the compiler must
-// otherwise assume to change it, so all of it arrives in one round of scalar loads.
+// otherwise assume to change it, so all of it arrives in one round of scalar loads.  That is more than
+// the scalar registers hold: 26 to 47 values wait in lanes of a vector register, which costs an
+// instruction each way, not a load.
 // VOL: blocks from nwin on fold the volumes of membranes with a volume penalty, one body each.
 // Nothing before the probes needs them, and a launch of their own cost a capsule in 75^3 4.2 us of a
 // 37 us step (now 33.5).  Without VOL the kernel keeps its registers: 64 jobs 639 us per step, 650 with

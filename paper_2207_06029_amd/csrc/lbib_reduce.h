@@ -26,13 +26,13 @@ __device__ __forceinline__ double gsum(double v) {
     return v;
 }
 
-// Deterministic per-body totals.  Every block of a body stores its partial sums (up to six
-// values, one row per value in the body's region); one block per body folds them in a later
-// launch (volumes: in a block of the moments launch), whose boundary makes the partials visible without a per-block device-scope release
-// (each of which would write back an L2).  Thread t takes blocks t, t+512, ... in order, then a
-// fixed tree (DPP within each wave, the eight waves in order) combines the 512 results; a block of
-// 256 threads takes the parts of t and t+256.  The order depends only on the body's own block count, so totals are bitwise reproducible and
-// independent of other jobs in the launch.
+// Deterministic per-body totals.  Every block of a body stores its partial sums (up to six values, one
+// row per value in the body's region); one block per body folds them in a later launch (volumes: in a
+// block of the moments launch), whose boundary makes the partials visible without a per-block
+// device-scope release (each of which would write back an L2).  Thread t takes blocks t, t+512, ... in
+// order, then a fixed tree (DPP within each wave, the eight waves in order) combines the 512 results; a
+// block of 256 threads takes the parts of t and t+256.  The order depends only on the body's own block
+// count, so totals are bitwise reproducible and independent of other jobs in the launch.
 constexpr int FOLD_THREADS = 512;   // threads of the fold block: 2048 partials per load round
 
 // A body's partials: value i of block k at 16 red_slot + i stride + k, stride = the body's larger
