@@ -54,6 +54,7 @@ template <typename S> struct Narrow;
 // cvt / st take the value in storage units.
 template <> struct Narrow<float> {
     static constexpr float ulp = 0.f;
+    static constexpr bool eight_waves = false;   // see k_sweep
     __device__ static __forceinline__ float cvt(float v, float) { return v; }
     __device__ static __forceinline__ void st(float* p, float v, float) { *p = v; }
 };
@@ -62,11 +63,13 @@ __device__ __forceinline__ float sr_perturb(float x, float d) {
 }
 template <> struct Narrow<__half> {
     static constexpr float ulp = 1.f / 1024.f;   // 10 stored mantissa bits
+    static constexpr bool eight_waves = true;
     __device__ static __forceinline__ __half cvt(float v, float d) { return __float2half_rn(sr_perturb(v, d)); }
     __device__ static __forceinline__ void st(__half* p, float v, float d) { *p = cvt(v, d); }
 };
 template <> struct Narrow<__hip_bfloat16> {
     static constexpr float ulp = 1.f / 128.f;    // 7 stored mantissa bits
+    static constexpr bool eight_waves = false;
     __device__ static __forceinline__ __hip_bfloat16 cvt(float v, float d) { return __float2bfloat16(sr_perturb(v, d)); }
     __device__ static __forceinline__ void st(__hip_bfloat16* p, float v, float d) { *p = cvt(v, d); }
 };
@@ -666,11 +669,12 @@ __device__ __forceinline__ void sweep_node(const Pools& P, const JobDev& J, cons
 // instead of one after the other at the start of every block.
 // Registers: the scalar ones bound the waves per SIMD too (800 per SIMD, in steps of 16), so the
 // compiler is held to 96 of them: eight waves instead of seven (64-job FP16 batch 664 -> 642 us per
-// step).  The 16-bit sweep of one lattice, the one with the most vector work per byte, is also
-// scheduled for eight waves (96x96x384 51.6 -> 49.1 us); FP32 lost 0.5 % by that, and the batched
-// 16-bit form spilled scalars (918 us).
+// step).  The FP16 sweep of one lattice, with the most vector work per byte, is also scheduled for
+// eight waves (96x96x384 51.6 -> 49.1 us).  FP32 lost 0.5 % by that, BF16 1 % (193^3 102.0 -> 103.5,
+// 256x128x256 127.2 -> 128.3: it spills vector registers), and the batched 16-bit form spilled scalars
+// (918 us).
 template <typename S, bool COLLIDE, int NPT, bool OFF32, bool ONE>
-__global__ void __launch_bounds__(1024, ONE && sizeof(S) == 2 ? 8 : 4) __attribute__((amdgpu_num_sgpr(96))) k_sweep(Pools P, int a_to_b, SweepOrder order) {
+__global__ void __launch_bounds__(1024, ONE && Narrow<S>::eight_waves ? 8 : 4) __attribute__((amdgpu_num_sgpr(96))) k_sweep(Pools P, int a_to_b, SweepOrder order) {
     const int tile = (int)sweep_tile(order, blockIdx.x);
     const int4 te = P.tiles[tile];
     const int job = ONE ? 0 : te.x;
