@@ -133,6 +133,7 @@ struct Batch {
     lbib_status retile();
     lbib_status set_shape(SweepShape s);
     lbib_status rebuild_bodies();
+    lbib_status build_body_tables();
     lbib_status download_body_state();
     lbib_status add_body(int job, const lbib_body_desc& d, const double* xyz, int nv,
                          const int* tri, int nt, int* id);

@@ -473,7 +473,6 @@ lbib_status Batch::set_shape(SweepShape s) {
     return retile();
 }
 
-// Re-create every body-related device pool from the host copies (after a body was added).
 // The record of body h in lattice J, without its placement (offsets and block ranges).
 void body_record(const HostBody& h, const JobDev& J, BodyDev& B) {
     std::memset(&B, 0, sizeof B);
@@ -513,7 +512,22 @@ void incidence_lists(const HostBody& h, int wt, int wh, std::vector<int>& vtl, s
     }
 }
 
+// Re-create every body-related device pool from the host copies (after a body was added).
 lbib_status Batch::rebuild_bodies() {
+    const lbib_status st = build_body_tables();
+    if (!st) return st;
+    // no table is whole: no launch may be made for a body
+    nbodies = 0;
+    nblk_c = nblk_e = nblk_t = nblk_v = nblk_u = nblk_w = 0;
+    any_rigid = any_volume = any_wide = false;
+    P.solo_job = -1;
+    for (auto& J : jobs) J.nbodies = 0;
+    (void)hipMemcpyAsync(d_jobs, jobs.data(), sizeof(JobDev) * jobs.size(), hipMemcpyHostToDevice, stream);
+    (void)hipStreamSynchronize(stream);
+    return st;
+}
+
+lbib_status Batch::build_body_tables() {
     lbib_status st;
     if ((st = download_body_state())) return st;
     HIP_TRY(hipStreamSynchronize(stream));
@@ -695,10 +709,12 @@ lbib_status Batch::add_body(int job, const lbib_body_desc& d, const double* xyz,
     hbodies.push_back(hb);
     st = rebuild_bodies();
     if (st) {
-        // drop the body again so the lattice stays usable
+        // drop the body again and go on with the others, from the state their host copies hold
+        const std::string why = last_error();
         for (size_t i = 0; i < hbodies.size(); ++i)
             if (hbodies[i].job == job && hbodies[i].local_id == local) { hbodies.erase(hbodies.begin() + i); break; }
-        return st;
+        if (rebuild_bodies()) hbodies.clear();   // not even those fit any more: the fluid alone
+        return fail(st, why);
     }
     *id = local;
     return LBIB_OK;

@@ -196,3 +196,38 @@ for T in (1, 7, 24, 63, 64, 65, 128, 200, 1000):
                 assert got == list(range(at + xcd * chunk, at + (xcd + 1) * chunk)), (T, chunk)
         assert order[8 * chunk * turns:] == list(range(8 * chunk * turns, T))
 """)
+
+
+def test_a_refused_body_leaves_the_lattice_as_it_was(stub):
+    """A body that a caller's workspace cannot hold is refused; steps after it run the bodies that were
+    there before, and no kernel for the one that was not."""
+    _run(stub, """
+spec = I.LatticeSpec(24, 24, 24, 0.8, **I.shear_walls(0.01))
+xyz, tri = I.spheroid_mesh(1, (3.5, 3.5, 2.8), (11.5,) * 3)
+body = I.BodySpec(rigid=0, ks0=0.01, kb=0.0, kv=0.0, mass_ratio=2.0)
+for bodies in (0, 1):
+    need = api.workspace_bytes(spec, len(xyz) * bodies, len(tri) * bodies) + 4096
+    buf = ctypes.create_string_buffer(need + 256)
+    lat = api.Lattice(spec, stream=4711, workspace_ptr=(ctypes.addressof(buf) + 255) // 256 * 256, workspace_bytes=need)
+    if bodies:
+        lat.set_velocity(lat.add_body(body, xyz, tri), np.full(3 * len(xyz), 0.25))
+    before = [lat.body_state(b) for b in range(bodies)]
+    try:
+        lat.add_body(body, xyz, tri)
+        assert False
+    except Exception as e:
+        assert "workspace too small" in str(e)
+    log()
+    lat.step(2)
+    names = {l.split()[1] for l in log()}
+    assert any("k_sweep" in n for n in names)
+    assert any("k_centroids" in n for n in names) == (bodies == 1)
+    for b in range(bodies):
+        for p, q in zip(before[b], lat.body_state(b)):
+            assert (p == q).all()
+    try:
+        lat.body_state(bodies)
+        assert False
+    except Exception as e:
+        assert "no such body" in str(e)
+""")
