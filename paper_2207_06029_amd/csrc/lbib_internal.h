@@ -80,10 +80,12 @@ constexpr bool table_ok() {
 static_assert(table_ok(), "D3Q19 tables inconsistent");
 
 // ---------------------------------------------------------------- tables
-// Elements from one population plane to the next in library-owned memory: planes start on 128 B
-// lines (both element sizes), so the sweep's stores fill whole lines also where the node count is odd.
-// Lines shared by two tiles are written in parts, by two XCDs: 193^3 FP32 sweeps in 202 us with
-// aligned planes, 264 us without (97^3 26.0 against 27.8, 135x131x141 73 against 85).
+// Elements from one population plane to the next in lattices and batches in library-owned memory: planes
+// start on 128 B lines (both element sizes), so the sweep's stores fill whole lines also where the node
+// count is odd.  Lines shared by two tiles are written in parts, by two XCDs: 193^3 FP32 sweeps in 202 us
+// with aligned planes, 264 us without (97^3 26.0 against 27.8, 135x131x141 73 against 85).  A caller's
+// workspace holds packed planes; a server slot takes the stride where its capacity has the room, but
+// starts on a line only if that capacity is a multiple of PLANE_ALIGN nodes.
 constexpr long long PLANE_ALIGN = 64;
 constexpr long long plane_stride(long long n) { return (n + PLANE_ALIGN - 1) / PLANE_ALIGN * PLANE_ALIGN; }
 
